@@ -230,6 +230,19 @@ RenderArgs render_args(const gs_projected* p, const gs_binning* b, const gs_opts
       a.log2_sh = sh;
     }
   }
+  // its ppt blocks of 64 pixels, by the same rule
+  const int log2_ppt = ilog2(o->pixels_per_thread);
+  best = -1;
+  for (int bx = 0; bx <= log2_ppt; ++bx) {
+    const int bw = a.log2_sw - bx, bh = a.log2_sh - (log2_ppt - bx);
+    if (bw < 0 || bh < 0) continue;
+    const int d = std::abs(bw - bh), dbest = std::abs(2 * a.log2_bw - 6);
+    if (best < 0 || d < dbest || (d == dbest && bw > a.log2_bw)) {
+      best = bx;
+      a.log2_bx = bx;
+      a.log2_bw = bw;
+    }
+  }
   a.batch = o->batch_depth;
   a.ppt = o->pixels_per_thread;
   a.cull = o->subtile_cull;

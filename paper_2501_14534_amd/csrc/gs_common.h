@@ -78,17 +78,16 @@ __device__ __forceinline__ float4 staged_b(float4 rb) {  // (c, o', radius, dept
 }
 
 // One (pixel, splat) evaluation shared bit-for-bit by the forward and the
-// backward walks (both stage the same scaled conic): square test, Gaussian
-// falloff G and alpha = min(0.99, o' G).  Every operation is explicit (fused
-// multiply-adds written out, no other contraction), so both kernels take
-// identical skip/stop decisions.  Computed without branching; returns the
-// square test's outcome.
+// backward walks (both stage the same scaled conic): Gaussian falloff G and
+// alpha = min(0.99, o' G).  Every operation is explicit (fused multiply-adds
+// written out, no other contraction), so both kernels take identical skip/stop
+// decisions.  Computed without branching; the square test is the caller's.
 struct Eval {
   float dx, dy, G, raw, alpha;
 };
 
-__device__ __forceinline__ bool eval_splat_all(float px, float py, float u, float v, float a, float b, float c,
-                                               float o, float rad, Eval* e) {
+__device__ __forceinline__ void eval_splat_all(float px, float py, float u, float v, float a, float b, float c,
+                                               float o, Eval* e) {
 #pragma clang fp contract(off)
   const float dx = px - u;
   const float dy = py - v;
@@ -101,7 +100,6 @@ __device__ __forceinline__ bool eval_splat_all(float px, float py, float u, floa
   e->G = G;
   e->raw = raw;
   e->alpha = fminf(kAlphaMax, raw);
-  return fabsf(dx) <= rad && fabsf(dy) <= rad;
 }
 
 // Sum over the 64 lanes of a wave, result valid in lane 63.  Row-local

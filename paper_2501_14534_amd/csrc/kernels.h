@@ -37,6 +37,7 @@ struct RenderArgs {
   int32_t log2_tw, log2_th;
   int32_t log2_sw, log2_sh;  // sub-tile (one per wave) width and height
   int32_t log2_sx;           // sub-tiles along x
+  int32_t log2_bw, log2_bx;  // 64-pixel blocks of a sub-tile (one per pixel of a thread): width, blocks along x
   int32_t batch;
   int32_t ppt;
   int32_t cull;

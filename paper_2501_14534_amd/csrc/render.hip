@@ -13,11 +13,22 @@
 //
 // Sub-tile culling (CULL): while staging a batch, each record's conservative
 // alpha >= 1/255 footprint (the ellipse q <= 2 ln(255 o'), widened by
-// rounding margins) is tested against the live-pixel box of every wave: its
-// bounding box first, then the ellipse itself (the minimum of q over the
-// box); each wave then walks only the records whose bit it holds, taken from
-// a ballot in scalar registers.  Culled records fail a per-pixel test for
-// every pixel of that wave, so the result is unchanged.
+// rounding margins) is tested against the live-pixel box of every 64-pixel
+// block (a wave has one block per pixel of a thread): its bounding box first,
+// then the ellipse itself (the minimum of q over the box); each wave then walks
+// only the records whose bits it holds, taken from ballots in scalar registers,
+// and of those only the blocks that they reach.  Culled records fail a
+// per-pixel test for every pixel of that block, so the result is unchanged.
+//
+// Both walks are bound by vector issue where tiles are large (6M Gaussians,
+// eight views up to 1080p, 32 x 32 tiles at 4 pixels a thread: 0.9 and 1.0 of
+// the issue rate; the records that a 16 x 16 sub-tile walks reach 2.5 of its 4
+// blocks, and composite in 34 of a block's 64 lanes).  Skipping blocks, keeping
+// every decision in scalar masks and selecting lanes through the exec mask took
+// the forward there from 1.75 to 1.36 ms and the backward from 3.30 to 2.59 ms;
+// at 1M Gaussians, 1600 x 1064, 32 x 16 tiles at 2, from 0.231 to 0.197 and
+// from 0.424 to 0.407 ms; with one block a wave (16 x 16 tiles, the same
+// scene's forward) from 0.217 to 0.191 ms.
 //
 // Forward: lanes whose pixels have terminated drop out of the walk through
 // the exec mask, and a wave leaves once all its pixels are done; the
@@ -64,64 +75,51 @@ __device__ __forceinline__ TileCtx tile_ctx(const ViewTable& vt, const RenderArg
 }
 
 // Pixels of a tile are split into one sub-tile per wave (as square as the
-// tile allows, chosen on the host); a lane covers PPT consecutive pixels of a
-// sub-tile row.  Pixel p of thread t:
-__device__ __forceinline__ void pixel_of(const RenderArgs& a, int ppt, int t, int p, int tx, int ty, int* x, int* y) {
+// tile allows, chosen on the host), and a sub-tile into PPT blocks of 64
+// pixels (as square as it allows: 8 x 8 for the usual tiles).  A lane covers
+// one pixel of each block, so that a wave can skip a block that a record does
+// not reach.  Pixel p of thread t:
+__device__ __forceinline__ void pixel_of(const RenderArgs& a, int t, int p, int tx, int ty, int* x, int* y) {
   const int w = t >> 6, l = t & (kWave - 1);
   const int sxi = w & ((1 << a.log2_sx) - 1), syi = w >> a.log2_sx;
-  const int li = l * ppt + p;
-  *x = (tx << a.log2_tw) + (sxi << a.log2_sw) + (li & ((1 << a.log2_sw) - 1));
-  *y = (ty << a.log2_th) + (syi << a.log2_sh) + (li >> a.log2_sw);
+  const int bxi = p & ((1 << a.log2_bx) - 1), byi = p >> a.log2_bx;
+  *x = (tx << a.log2_tw) + (sxi << a.log2_sw) + (bxi << a.log2_bw) + (l & ((1 << a.log2_bw) - 1));
+  *y = (ty << a.log2_th) + (syi << a.log2_sh) + (byi << (6 - a.log2_bw)) + (l >> a.log2_bw);
 }
+
+// Index of pixel p of this thread in the per-tile arrays of the workspace
+// (consecutive threads next to each other).
+__device__ __forceinline__ int tile_pixel(int p) { return p * (int)blockDim.x + (int)threadIdx.x; }
 
 // Box of pixel centres [x0, x1] x [y0, y1]; empty when x0 > x1.
 struct Box {
   float x0, x1, y0, y1;
 };
 
-// Box of the pixel centres of this wave's lanes whose pixel is still live
-// (may still composite or receive gradient), the same value in every lane.
-// Culling against it instead of the wave's whole sub-tile drops the records
-// that can only reach pixels that have already stopped.
-// Min (or max) over the 64 lanes, returned in every lane: row shifts by 1, 2,
-// 4, 8 leave each 16-lane row's result in its lane 15, row broadcasts 15 and
-// 31 fold the rows into lane 63 (lanes without a source see the identity).
-template <bool MAX>
-__device__ __forceinline__ float wave_minmax(float v) {
-  const int id = __builtin_bit_cast(int, MAX ? -__builtin_inff() : __builtin_inff());
-  auto step = [&](float x, float y) { return MAX ? fmaxf(x, y) : fminf(x, y); };
-#define GS_DPP_STEP(ctrl, rmask) \
-  v = step(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(id, __builtin_bit_cast(int, v), ctrl, rmask, 0xf, false)))
-  GS_DPP_STEP(0x111, 0xf);
-  GS_DPP_STEP(0x112, 0xf);
-  GS_DPP_STEP(0x114, 0xf);
-  GS_DPP_STEP(0x118, 0xf);
-  GS_DPP_STEP(0x142, 0xa);
-  GS_DPP_STEP(0x143, 0xc);
-#undef GS_DPP_STEP
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), kWave - 1));
-}
-
-template <int PPT>
-__device__ __forceinline__ Box live_box(const float (&px)[PPT], const float (&py)[PPT], const bool (&live)[PPT]) {
-  Box b{__builtin_inff(), -__builtin_inff(), __builtin_inff(), -__builtin_inff()};
-#pragma unroll
-  for (int p = 0; p < PPT; ++p)
-    if (live[p]) {
-      b.x0 = fminf(b.x0, px[p]);
-      b.x1 = fmaxf(b.x1, px[p]);
-      b.y0 = fminf(b.y0, py[p]);
-      b.y1 = fmaxf(b.y1, py[p]);
-    }
-  b.x0 = wave_minmax<false>(b.x0);
-  b.x1 = wave_minmax<true>(b.x1);
-  b.y0 = wave_minmax<false>(b.y0);
-  b.y1 = wave_minmax<true>(b.y1);
+// Box of the pixel centres of a block's live pixels (those that may still
+// composite or receive gradient), the same value in every lane; empty when
+// none is live.  Culling against it instead of the whole block drops the
+// records that can only reach pixels that have already stopped.  `m`: the live
+// lanes; (ox, oy): the block's first pixel centre, the same in every lane.
+// Rows and columns come from the ballot by scalar bit operations, beside the
+// vector units.
+__device__ __forceinline__ Box live_box(uint64_t m, int log2_bw, float ox, float oy) {
+  if (m == 0) return Box{__builtin_inff(), -__builtin_inff(), __builtin_inff(), -__builtin_inff()};
+  uint64_t c = m;  // the rows folded into the first
+  for (int s = 32; s >> log2_bw; s >>= 1) c |= c >> s;
+  if (log2_bw < 6) c &= (1ull << (1 << log2_bw)) - 1;
+  Box b;
+  b.x0 = ox + (float)__builtin_ctzll(c);
+  b.x1 = ox + (float)(63 - __builtin_clzll(c));
+  b.y0 = oy + (float)(__builtin_ctzll(m) >> log2_bw);
+  b.y1 = oy + (float)((63 - __builtin_clzll(m)) >> log2_bw);
   return b;
 }
 
-// Bit w set when record (u, v, conic, o', radius) may composite some pixel in
-// wave w's live box.
+__device__ __forceinline__ float first_lane(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+
 // Minimum over the box dx in [X0, X1], dy in [Y0, Y1] (relative to the
 // centre) of q = A dx^2 + 2 B dx dy + C dy^2, positive definite: 0 when the
 // centre is inside, else on an edge, where the 1-D minimiser is clamped to
@@ -135,7 +133,11 @@ __device__ __forceinline__ float qmin_box(float A, float B, float C, float iA, f
   return fminf(fminf(qv(X0, dyx0), qv(X1, dyx1)), fminf(qv(dxy0, Y0), qv(dxy1, Y1)));
 }
 
-__device__ __forceinline__ uint32_t footprint_mask(float4 ra, float4 rb, int nwaves, const Box* boxes) {
+// Bit w set when record (u, v, conic, o', radius) may composite some pixel in
+// box w of nboxes.
+// Hardware reciprocals, roots and logarithms (a few units in the last place)
+// are far inside the margins; where one overflows, the square decides.
+__device__ __forceinline__ uint32_t footprint_mask(float4 ra, float4 rb, int nboxes, const Box* boxes) {
   const float u = ra.x, v = ra.y, A = ra.z, B = ra.w, C = rb.x, o = rb.y, r = rb.z;
   if (!(o >= kAlphaMin * 0.999f)) return 0u;  // alpha <= o' < 1/255 at every pixel
   float ex = r, ey = r, qm = 0.f, iA = 0.f, iC = 0.f;
@@ -143,21 +145,23 @@ __device__ __forceinline__ uint32_t footprint_mask(float4 ra, float4 rb, int nwa
   const float det = A * C - B * B;
   if (det > 0.f) {
     const float tr = 0.5f * (A + C);
-    const float lmax = tr + sqrtf(fmaxf(0.f, tr * tr - det));
+    const float lmax = tr + __builtin_amdgcn_sqrtf(fmaxf(0.f, tr * tr - det));
     if (lmax * lmax <= 1e3f * det) {  // condition number <= 1e3: rounding of q stays far below the margins
-      qm = 2.0f * __logf(255.0f * o) * 1.002f + 0.002f;
-      const float idet = 1.0f / det;
-      ex = fminf(r, sqrtf(fmaxf(qm, 0.f) * C * idet) * 1.001f + 0.01f);
-      ey = fminf(r, sqrtf(fmaxf(qm, 0.f) * A * idet) * 1.001f + 0.01f);
-      iA = 1.0f / A;
-      iC = 1.0f / C;
+      // 2 ln(255 o') = 2 ln 2 (log2 255 + log2 o')
+      qm = (2.0f * 0.69314718f * 1.002f) * (7.99435344f + __builtin_amdgcn_logf(o)) + 0.002f;
+      const float k = fmaxf(qm, 0.f) * __builtin_amdgcn_rcpf(det);
+      ex = fminf(r, __builtin_amdgcn_sqrtf(k * C) * 1.001f + 0.01f);
+      ey = fminf(r, __builtin_amdgcn_sqrtf(k * A) * 1.001f + 0.01f);
+      iA = __builtin_amdgcn_rcpf(A);
+      iC = __builtin_amdgcn_rcpf(C);
       exact = true;
     }
   }
   ex += 0.5f;
   ey += 0.5f;
   uint32_t m = 0u;
-  for (int w = 0; w < nwaves; ++w) {
+#pragma unroll
+  for (int w = 0; w < nboxes; ++w) {
     const Box b = boxes[w];
     bool hit = (u + ex >= b.x0) && (u - ex <= b.x1) && (v + ey >= b.y0) && (v - ey <= b.y1);
     // the ellipse q <= qm against the box of pixel centres (widened by 1e-3 px):
@@ -170,15 +174,23 @@ __device__ __forceinline__ uint32_t footprint_mask(float4 ra, float4 rb, int nwa
 }
 
 // Entry selection.  Once a batch is staged, lane l of wave w reads the
-// footprint mask of entry 64c + l; the ballot is the set of entries of chunk c
-// that wave w walks.  The walk takes the set bits in order from scalar
-// registers, so no per-wave index list is built, stored or read.
-template <bool CULL>
-__device__ __forceinline__ uint64_t chunk_bits(const uint8_t* s_mask, int c, int cnt, int wave, int lane) {
+// footprint mask of entry 64c + l; ballot p is the set of entries of chunk c
+// that reach block p of wave w, returned with their union.  The walk takes the
+// set bits in order from scalar registers, so no per-wave index list is built,
+// stored or read.
+template <int PPT, bool CULL>
+__device__ __forceinline__ uint64_t chunk_bits(const uint16_t* s_mask, int c, int cnt, int wave, int lane,
+                                               uint64_t (&mp)[PPT]) {
   const int i = c * kWave + lane;
-  bool bit = i < cnt;
-  if (CULL && bit) bit = ((s_mask[i] >> wave) & 1u) != 0u;
-  return __ballot(bit);
+  uint32_t bits = i < cnt ? (1u << PPT) - 1u : 0u;
+  if (CULL && bits) bits &= (uint32_t)s_mask[i] >> (wave * PPT);
+  uint64_t m = 0;
+#pragma unroll
+  for (int p = 0; p < PPT; ++p) {
+    mp[p] = __ballot((bits >> p) & 1u);
+    m |= mp[p];
+  }
+  return m;
 }
 
 // Dynamic LDS of the blend kernels, sized by the batch depth B and the wave count W:
@@ -187,13 +199,13 @@ struct Lds {
   float4 *a, *b, *c;
   uint32_t* e;
   float* part;
-  uint8_t* mask;
+  uint16_t* mask;
 };
 
 __host__ __device__ inline size_t lds_bytes(int batch, int nwaves, bool bwd) {
   size_t o = 3 * 16 * (size_t)batch;
   if (bwd) o += 4 * (size_t)batch + 4 * (size_t)GS_GRAD_FLOATS * nwaves * batch;
-  o += (size_t)batch;
+  o += 2 * (size_t)batch;
   return (o + 15) & ~(size_t)15;
 }
 
@@ -209,7 +221,7 @@ __device__ inline Lds lds_carve(unsigned char* base, int batch, int nwaves, bool
     l.e = (uint32_t*)(base + o), o += 4 * (size_t)batch;
     l.part = (float*)(base + o), o += 4 * (size_t)GS_GRAD_FLOATS * nwaves * batch;
   }
-  l.mask = base + o;
+  l.mask = (uint16_t*)(base + o);
   return l;
 }
 
@@ -221,6 +233,15 @@ __host__ __device__ inline int bwd_batch(int batch, int nwaves) {
 
 __device__ __forceinline__ int tile_of_block(const RenderArgs& a) {
   return a.order ? (int)a.order[blockIdx.x] : (int)blockIdx.x;
+}
+
+// Whether this lane's bit is set in a wave mask.
+__device__ __forceinline__ bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+// The lanes whose pixel lies in the square of radius `rad` about an evaluated
+// splat.  Decisions are kept as wave masks in scalar registers: they are
+// combined beside the vector units and select lanes through the exec mask.
+__device__ __forceinline__ uint64_t lanes_inside(const Eval& e, float rad) {
+  return __ballot(fabsf(e.dx) <= rad) & __ballot(fabsf(e.dy) <= rad);
 }
 
 // Cross-lane moves of the backward's reduce-scatter.  permlane32_swap
@@ -311,10 +332,12 @@ __device__ __forceinline__ float reduce_scatter9(const float (&x)[GS_GRAD_FLOATS
 // about three chunks instead of its whole list.
 enum : int { kFull = 0, kCount = 1, kTPass = 2 };
 constexpr int kHalves = 2;  // entries a lane stages per forward group
-// records evaluated together by the forward walk: four independent chains a
-// lane (PPT pixels per record)
-template <int PPT>
-constexpr int ilp_records() { return PPT >= 4 ? 1 : 4 / PPT; }
+// Pixel abscissa of a pixel that has stopped, or lies outside the image: NaN,
+// which no record's square holds (an infinite radius included), so the walk
+// needs no flag per pixel.
+constexpr float kStopped = __builtin_nanf("");
+__device__ __forceinline__ bool stopped(float px) { return px != px; }
+constexpr int kIlp = 4;     // records evaluated together by the forward walk at one pixel per thread
 
 // Stores and loads of the values one work item hands to another within a
 // launch (image, T_final, last_contrib, chunk states).  COH: agent-scope
@@ -396,19 +419,23 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
   // apart so that the colour after a boundary is a sum of non-negative
   // segments, accurate relative to itself)
   float px[PPT], py[PPT], T[PPT], C0[PPT], C1[PPT], C2[PPT], S0[PPT], S1[PPT], S2[PPT];
+  float ox[PPT], oy[PPT];
   int last[PPT];
-  bool done[PPT];
 #pragma unroll
   for (int p = 0; p < PPT; ++p) {
     int x, y;
-    pixel_of(a, PPT, threadIdx.x, p, tc.tx, tc.ty, &x, &y);
+    pixel_of(a, threadIdx.x, p, tc.tx, tc.ty, &x, &y);
     px[p] = (float)x + 0.5f;
     py[p] = (float)y + 0.5f;
     T[p] = 1.0f;
     C0[p] = C1[p] = C2[p] = 0.0f;
     S0[p] = S1[p] = S2[p] = 0.0f;
     last[p] = 0;
-    done[p] = !(x < va.W && y < va.H);
+    if (CULL) {  // lane 0 holds the block's first pixel
+      ox[p] = first_lane(px[p]);
+      oy[p] = first_lane(py[p]);
+    }
+    if (!(x < va.W && y < va.H)) px[p] = kStopped;
   }
 
   const int tpx = 1 << (a.log2_tw + a.log2_th);
@@ -422,16 +449,17 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
     for (int p = 0; p < PPT; ++p) {
       float t = 1.0f;
       for (uint32_t j = 1; j <= kf; ++j)
-        t *= a.fprod[(int64_t)(((uint64_t)tc.start + ((uint64_t)j << lf)) >> lf) * tpx + threadIdx.x * PPT + p];
+        t *= a.fprod[(int64_t)(((uint64_t)tc.start + ((uint64_t)j << lf)) >> lf) * tpx + tile_pixel(p)];
       T[p] = t;
-      dead[p] = !done[p] && t < kTMin;
-      done[p] = done[p] || dead[p];
+      dead[p] = !stopped(px[p]) && t < kTMin;
+      if (dead[p]) px[p] = kStopped;
     }
   }
   if (TPASS) {  // only the pixels still going after chunk 0
     const float* p0 = a.fprod + (int64_t)(((uint64_t)tc.start + (1ull << lf)) >> lf) * tpx;
 #pragma unroll
-    for (int p = 0; p < PPT; ++p) done[p] = done[p] || p0[threadIdx.x * PPT + p] < kTMin;
+    for (int p = 0; p < PPT; ++p)
+      if (p0[tile_pixel(p)] < kTMin) px[p] = kStopped;
   }
   int nbnd = 0;  // chunk boundaries this wave recorded (uniform in the wave)
   // first backward boundary this walk can record: the first multiple of 2^lc
@@ -485,13 +513,13 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
     }
   }
   while (gs < ce) {
-    bool alive = false, live[PPT];
+    uint64_t live[PPT], alive = 0;
 #pragma unroll
     for (int p = 0; p < PPT; ++p) {
-      live[p] = !done[p];
+      live[p] = __ballot(!stopped(px[p]));
       alive |= live[p];
     }
-    if (__ballot(alive) == 0) break;  // every pixel of this wave has stopped
+    if (alive == 0) break;  // every pixel of this wave has stopped
     const uint64_t rel = gs - tc.start;
     if (MODE == kFull && rel != 0 && (rel & ((1ull << lc) - 1)) == 0) {
       // a chunk boundary of the backward: record each pixel's transmittance
@@ -500,26 +528,29 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
       float4* st = a.state + slot * tpx;
 #pragma unroll
       for (int p = 0; p < PPT; ++p) {
-        put4<COH>(st + threadIdx.x * PPT + p, make_float4(T[p], S0[p], S1[p], S2[p]));
+        put4<COH>(st + tile_pixel(p), make_float4(T[p], S0[p], S1[p], S2[p]));
         S0[p] = S1[p] = S2[p] = 0.0f;
       }
       if (lane == 0) a.slot_owner[slot] = (uint32_t)gtile;  // every wave that gets here writes the same
       ++nbnd;
     }
     const int cnt = (int)(ge - gs);
-    Box box;
-    if (CULL) box = live_box<PPT>(px, py, live);  // all lanes: a cross-lane reduction
-    bool bits[kHalves];
+    Box box[PPT];
+    if (CULL) {
+#pragma unroll
+      for (int p = 0; p < PPT; ++p) box[p] = live_box(live[p], a.log2_bw, ox[p], oy[p]);
+    }
+    uint32_t bits[kHalves];  // the blocks that the entry may reach
     uint32_t gid[kHalves];
 #pragma unroll
     for (int h = 0; h < kHalves; ++h) {
       const int e = h * (int)GH + lane;
-      bits[h] = e < cnt;
+      bits[h] = e < cnt ? (1u << PPT) - 1u : 0u;
       if (bits[h]) {  // entry e from the registers
         s_a[e] = staged_a(ra[h]);
         s_b[e] = staged_b(rb[h]);
         if (!COUNT) s_c[e] = rc[h];
-        if (CULL) bits[h] = footprint_mask(ra[h], rb[h], 1, &box) != 0u;
+        if (CULL) bits[h] = footprint_mask(ra[h], rb[h], PPT, box);
       }
       gid[h] = rid[h];
     }
@@ -540,73 +571,109 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
     wave_lds_sync();  // the staged group is visible to the whole wave
 #pragma unroll
     for (int h = 0; h < kHalves; ++h) {
-    uint64_t m = __ballot(bits[h]);
-    if (m != 0) {
-      // composite one evaluated record into this lane's pixel(s); branch-free: a
-      // lane that skips the splat adds exact zeros
-      auto composite = [&](int j, const Eval (&e)[PPT], const bool (&inside)[PPT], const float4& rc) {
-        const int idx = (int)(gs + j - tc.start) + 1;
-        uint32_t taken = 0;  // COUNT: pixels of this wave that composite record j
+    uint64_t mp[PPT], m = 0;  // the entries that reach block p, and their union
 #pragma unroll
-        for (int p = 0; p < PPT; ++p) {
-          const bool use = !done[p] && inside[p] && !(e[p].alpha < kAlphaMin);
-          const float Tn = T[p] * (1.0f - e[p].alpha);
-          const bool stop = use && Tn < kTMin;  // stop before this splat
-          done[p] = done[p] || stop;
-          // the product pass multiplies the stopping splat in as well
-          const bool take = TPASS ? use : use && !stop;
-          const float w = take ? e[p].alpha * T[p] : 0.0f;
+    for (int p = 0; p < PPT; ++p) {
+      mp[p] = __ballot((bits[h] >> p) & 1u);
+      m |= mp[p];
+    }
+    if (m != 0) {
+      // composite one evaluated record into this lane's pixel p.  `gone`: the
+      // lanes whose pixel has stopped since its square tests were made.  Returns
+      // the lanes that take the record.  With several blocks a record's lanes
+      // are selected through the exec mask (three vector operations fewer);
+      // with one they are selected by value, without the branch that would
+      // separate the records' independent evaluations.
+      auto composite = [&](int p, int j, const Eval& e, uint64_t inside, uint64_t& gone, const float4& rc) {
+        const int idx = (int)(gs + j - tc.start) + 1;
+        const float Tn = T[p] * (1.0f - e.alpha);
+        const uint64_t use = inside & ~gone & __ballot(!(e.alpha < kAlphaMin)), low = __ballot(Tn < kTMin);
+        gone |= use & low;  // stop before this splat
+        // the product pass multiplies the stopping splat in as well
+        const uint64_t take = TPASS ? use : use & ~low;
+        const bool in = lane_in(take);
+        if (PPT == 1 || in) {
+          const float w = PPT > 1 || in ? e.alpha * T[p] : 0.0f;
           C0[p] += rc.x * w;
           C1[p] += rc.y * w;
           C2[p] += rc.z * w;
           S0[p] += rc.x * w;
           S1[p] += rc.y * w;
           S2[p] += rc.z * w;
-          T[p] = take ? Tn : T[p];
-          last[p] = take ? idx : last[p];
-          if (COUNT) taken += (uint32_t)__popcll(__ballot(take));
+          T[p] = PPT > 1 || in ? Tn : T[p];
+          last[p] = PPT > 1 || in ? idx : last[p];
         }
+        return take;
+      };
+      auto stop = [&](int p, uint64_t gone) { px[p] = lane_in(gone) ? kStopped : px[p]; };
+      // COUNT: pixels of this wave that composite record j
+      auto count = [&](int j, uint32_t taken) {
         if (COUNT && lane == 0 && taken != 0) s_hits[j] += taken;
       };
-      // R records at a time (in list order) while R are left: their falloff
-      // and alpha do not depend on the transmittance, so the R evaluations run
-      // as independent chains before the R dependent compositing steps (no
-      // record is guarded on its own, which would let the compiler sink each
-      // evaluation next to its compositing step and serialise the
-      // exponentials' latencies); the last ones one at a time.
       const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-      auto eval_one = [&](int j, Eval (&e)[PPT], bool (&in)[PPT], float4& rc) {
-        const float4 ra = s_a[j], rb = s_b[j];
-        rc = COUNT ? zero4 : s_c[j];
-#pragma unroll
-        for (int p = 0; p < PPT; ++p)
-          in[p] = eval_splat_all(px[p], py[p], ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, rb.z, &e[p]);
-      };
-      constexpr int R = ilp_records<PPT>();
       const int hoff = h * (int)GH;  // bit b of m is entry hoff + b
-      while (m != 0) {
-        if (R == 1 || __popcll(m) >= R) {  // wave-uniform
-          int jq[R];
+      if constexpr (PPT == 1) {
+        // kIlp records at a time (in list order) while that many are left: their
+        // falloff and alpha do not depend on the transmittance, so the
+        // evaluations run as independent chains before the dependent compositing
+        // steps (no record is guarded on its own, which would let the compiler
+        // sink each evaluation next to its compositing step and serialise the
+        // exponentials' latencies); the last ones one at a time.
+        auto eval_one = [&](int j, Eval& e, uint64_t& in, float4& rc) {
+          const float4 ra = s_a[j], rb = s_b[j];
+          rc = COUNT ? zero4 : s_c[j];
+          eval_splat_all(px[0], py[0], ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, &e);
+          in = lanes_inside(e, rb.z);
+        };
+        uint64_t gone = 0;
+        while (m != 0) {
+          if (__popcll(m) >= kIlp) {  // wave-uniform
+            int jq[kIlp];
 #pragma unroll
-          for (int q = 0; q < R; ++q) {
-            jq[q] = hoff + __builtin_ctzll(m);
+            for (int q = 0; q < kIlp; ++q) {
+              jq[q] = hoff + __builtin_ctzll(m);
+              m &= m - 1;
+            }
+            float4 rcq[kIlp];
+            Eval eq[kIlp];
+            uint64_t iq[kIlp];
+#pragma unroll
+            for (int q = 0; q < kIlp; ++q) eval_one(jq[q], eq[q], iq[q], rcq[q]);
+#pragma unroll
+            for (int q = 0; q < kIlp; ++q) {
+              const uint64_t take = composite(0, jq[q], eq[q], iq[q], gone, rcq[q]);
+              if (COUNT) count(jq[q], (uint32_t)__popcll(take));
+            }
+          } else {
+            const int j = hoff + __builtin_ctzll(m);
             m &= m - 1;
+            float4 rc;
+            Eval e;
+            uint64_t in;
+            eval_one(j, e, in, rc);
+            const uint64_t take = composite(0, j, e, in, gone, rc);
+            if (COUNT) count(j, (uint32_t)__popcll(take));
           }
-          float4 rcq[R];
-          Eval eq[R][PPT];
-          bool iq[R][PPT];
+        }
+        stop(0, gone);
+      } else {
+        // one record at a time, over the blocks that it reaches (wave-uniform
+        // branches)
+        for (; m != 0; m &= m - 1) {
+          const int b = __builtin_ctzll(m), j = hoff + b;
+          const float4 ra = s_a[j], rb = s_b[j], rc = COUNT ? zero4 : s_c[j];
+          uint32_t taken = 0;
 #pragma unroll
-          for (int q = 0; q < R; ++q) eval_one(jq[q], eq[q], iq[q], rcq[q]);
-#pragma unroll
-          for (int q = 0; q < R; ++q) composite(jq[q], eq[q], iq[q], rcq[q]);
-        } else {
-          const int j = hoff + __builtin_ctzll(m);
-          m &= m - 1;
-          float4 rc;
-          Eval e[PPT];
-          bool in[PPT];
-          eval_one(j, e, in, rc);
-          composite(j, e, in, rc);
+          for (int p = 0; p < PPT; ++p)
+            if ((mp[p] >> b) & 1ull) {
+              Eval e;
+              eval_splat_all(px[p], py[p], ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, &e);
+              uint64_t gone = 0;
+              const uint64_t take = composite(p, j, e, lanes_inside(e, rb.z), gone, rc);
+              stop(p, gone);
+              if (COUNT) taken += (uint32_t)__popcll(take);
+            }
+          if (COUNT) count(j, taken);
         }
       }
       if (COUNT) {
@@ -630,7 +697,7 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
   if (TPASS) {  // the product, at the boundary that ends this chunk
     float* fp = a.fprod + (int64_t)((uint64_t)ce >> lf) * tpx;
 #pragma unroll
-    for (int p = 0; p < PPT; ++p) fp[threadIdx.x * PPT + p] = T[p];
+    for (int p = 0; p < PPT; ++p) fp[tile_pixel(p)] = T[p];
     return 0;
   }
   // Each recorded state becomes (T there, colour composited after it within
@@ -646,7 +713,7 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
       if (k0 - i < 0) break;  // wave-uniform
       const int64_t slot = (int64_t)((b0 + ((uint64_t)(k0 - i) << lc)) >> lc);
 #pragma unroll
-      for (int p = 0; p < PPT; ++p) v[i][p] = get4<COH>(a.state + slot * tpx + threadIdx.x * PPT + p);
+      for (int p = 0; p < PPT; ++p) v[i][p] = get4<COH>(a.state + slot * tpx + tile_pixel(p));
     }
 #pragma unroll
     for (int i = 0; i < kSuf; ++i) {
@@ -655,7 +722,7 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
 #pragma unroll
       for (int p = 0; p < PPT; ++p) {
         const float e0 = v[i][p].y, e1 = v[i][p].z, e2 = v[i][p].w;  // colour of the chunk before the boundary
-        put4<COH>(a.state + slot * tpx + threadIdx.x * PPT + p, make_float4(v[i][p].x, S0[p], S1[p], S2[p]));
+        put4<COH>(a.state + slot * tpx + tile_pixel(p), make_float4(v[i][p].x, S0[p], S1[p], S2[p]));
         S0[p] = e0 + S0[p];
         S1[p] = e1 + S1[p];
         S2[p] = e2 + S2[p];
@@ -671,9 +738,9 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
     const int64_t idx = kf + 1 < nfc ? (int64_t)((uint64_t)ce >> lf) : a.nfslots + (int64_t)((uint64_t)cs >> lf);
 #pragma unroll
     for (int p = 0; p < PPT; ++p) {
-      a.fres[idx * tpx + threadIdx.x * PPT + p] = make_float4(C0[p], C1[p], C2[p], T[p]);
-      a.flast[idx * tpx + threadIdx.x * PPT + p] = dead[p] ? -1 : last[p];
-      if (kf == 0) a.fprod[idx * tpx + threadIdx.x * PPT + p] = done[p] ? 0.0f : T[p];
+      a.fres[idx * tpx + tile_pixel(p)] = make_float4(C0[p], C1[p], C2[p], T[p]);
+      a.flast[idx * tpx + tile_pixel(p)] = dead[p] ? -1 : last[p];
+      if (kf == 0) a.fprod[idx * tpx + tile_pixel(p)] = stopped(px[p]) ? 0.0f : T[p];
     }
     return 0;
   }
@@ -681,7 +748,8 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
   int my_max = 0;
 #pragma unroll
   for (int p = 0; p < PPT; ++p) {
-    const int x = (int)px[p], y = (int)py[p];
+    int x, y;
+    pixel_of(a, threadIdx.x, p, tc.tx, tc.ty, &x, &y);
     if (x < va.W && y < va.H) {
       const int64_t pix = (int64_t)y * va.W + x;
       float* img = image + 3 * (int64_t)va.pix_off;
@@ -697,9 +765,12 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
 }
 
 // Work items [item_base, item_base + gridDim.x) of a forward walk, one per workgroup.
-// At one pixel a thread the kernel is held to 80 registers (six waves per SIMD).
+// The kernel is held to 80, 96 and 128 registers at 1, 2 and 4 pixels a thread
+// (six, five and four waves per SIMD).
+template <int PPT>
+constexpr int fwd_waves() { return PPT == 1 ? 6 : PPT == 2 ? 5 : 4; }
 template <int PPT, bool CULL, int MODE>
-__global__ __launch_bounds__(256, PPT == 1 ? 6 : 1) void render_fwd_kernel(RenderArgs a, ViewTable vt,
+__global__ __launch_bounds__(256, fwd_waves<PPT>()) void render_fwd_kernel(RenderArgs a, ViewTable vt,
                                                                            float* __restrict__ image,
                                                                            float* __restrict__ T_final,
                                                                            int32_t* __restrict__ last_out,
@@ -730,8 +801,8 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(RenderArgs a, ViewTabl
 #pragma unroll
   for (int p = 0; p < PPT; ++p) {
     int x, y;
-    pixel_of(a, PPT, threadIdx.x, p, tc.tx, tc.ty, &x, &y);
-    const int q = threadIdx.x * PPT + p;
+    pixel_of(a, threadIdx.x, p, tc.tx, tc.ty, &x, &y);
+    const int q = tile_pixel(p);
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, Tf = 1.f;
     bool have_T = false;
     int last = 0;
@@ -799,7 +870,7 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
                                          float* __restrict__ grad_pair, int64_t item, unsigned char* smem,
                                          bool ok = true, int walked = -1) {
   __shared__ int s_max[4];
-  __shared__ Box s_box[4];
+  __shared__ Box s_box[4 * PPT];  // live box of every wave's blocks
   const int lg = a.log2_chunk;
   int gtile;
   bool first;
@@ -832,7 +903,7 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
   float4* s_c = L.c;
   uint32_t* s_e = L.e;
   float* s_part = L.part;  // per-wave partial sums of one batch: [nwaves][batch][9]
-  uint8_t* s_mask = L.mask;
+  uint16_t* s_mask = L.mask;
 
   // this lane's element of the reduce-scatter (see reduce_scatter9)
   const bool b2 = (lane >> 2) & 1, b3 = (lane >> 3) & 1;
@@ -849,7 +920,7 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
 #pragma unroll
   for (int p = 0; p < PPT; ++p) {
     int x, y;
-    pixel_of(a, PPT, threadIdx.x, p, tc.tx, tc.ty, &x, &y);
+    pixel_of(a, threadIdx.x, p, tc.tx, tc.ty, &x, &y);
     px[p] = (float)x + 0.5f;
     py[p] = (float)y + 0.5f;
     T[p] = 1.0f;
@@ -914,10 +985,10 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
 #pragma unroll
     for (int p = 0; p < PPT; ++p) {
       if (lc[p] > rel) {
-        const float4 v = get4<L2>(st + threadIdx.x * PPT + p);
+        const float4 v = get4<L2>(st + tile_pixel(p));
         float c0 = v.y, c1 = v.z, c2 = v.w;
         if (sf) {
-          const float4 w = sf[threadIdx.x * PPT + p];
+          const float4 w = sf[tile_pixel(p)];
           c0 += w.x;
           c1 += w.y;
           c2 += w.z;
@@ -935,11 +1006,12 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
     const int cnt = (int)(be - bs);
     if (CULL) {
       // live pixels: those with an entry of this batch before their last contributor
-      bool live[PPT];
 #pragma unroll
-      for (int p = 0; p < PPT; ++p) live[p] = lc[p] > (int)(bs - tc.start);
-      const Box b = live_box<PPT>(px, py, live);
-      if (lane == 0) s_box[wave] = b;
+      for (int p = 0; p < PPT; ++p) {
+        const uint64_t live = __ballot(lc[p] > (int)(bs - tc.start));
+        const Box b = live_box(live, a.log2_bw, first_lane(px[p]), first_lane(py[p]));
+        if (lane == 0) s_box[wave * PPT + p] = b;
+      }
       __syncthreads();
     }
     for (int i = threadIdx.x; i < cnt; i += nthreads) {
@@ -950,47 +1022,55 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
       s_a[i] = staged_a(ra);
       s_b[i] = staged_b(rb);
       s_c[i] = a.splats[(size_t)rec * 3 + 2];
-      if (CULL) s_mask[i] = (uint8_t)footprint_mask(ra, rb, nwaves, s_box);
+      if (CULL) s_mask[i] = (uint16_t)footprint_mask(ra, rb, nwaves * PPT, s_box);
     }
     for (int i = threadIdx.x; i < nwaves * batch * GS_GRAD_FLOATS; i += nthreads) s_part[i] = 0.0f;
     __syncthreads();
     const int nchunks = (cnt + kWave - 1) / kWave;
     for (int c = nchunks - 1; c >= 0; --c) {
-      uint64_t m = chunk_bits<CULL>(s_mask, c, cnt, wave, lane);
+      uint64_t mp[PPT];
+      uint64_t m = chunk_bits<PPT, CULL>(s_mask, c, cnt, wave, lane, mp);
       if (m == 0) continue;
       // one staged record: per-pixel partials, then the wave's sums into LDS
       auto grad = [&](int j, const float4& ra, const float4& rb, const float4& rc) {
         const int jr = (int)(bs - tc.start) + j;                   // index within the tile's list
-        const float hb = 0.5f * ra.w;                              // staged b / 2 = k B
-        float x[GS_GRAD_FLOATS] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // u v A B C o' r g b
-        bool any = false;
+        float x[GS_GRAD_FLOATS] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // m dx, m dy, A B C o' r g b
+        uint64_t any = 0;
 #pragma unroll
         for (int p = 0; p < PPT; ++p) {
-          // branch-free: lanes that do not composite this splat add exact zeros
+          if (PPT > 1 && !((mp[p] >> (j - c * kWave)) & 1ull)) continue;  // wave-uniform: the block is not reached
           Eval e;
-          const bool inside = eval_splat_all(px[p], py[p], ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, rb.z, &e);
-          const bool use = jr < lc[p] && inside && !(e.alpha < kAlphaMin);
+          eval_splat_all(px[p], py[p], ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, &e);
+          const uint64_t use = lanes_inside(e, rb.z) & __ballot(jr < lc[p]) & __ballot(!(e.alpha < kAlphaMin));
           any |= use;
-          const float inv = __builtin_amdgcn_rcpf(1.0f - e.alpha);
-          T[p] = use ? T[p] * inv : T[p];  // transmittance in front of this splat
-          const float wgt = use ? e.alpha * T[p] : 0.0f;
-          x[6] += wgt * g0[p];
-          x[7] += wgt * g1[p];
-          x[8] += wgt * g2[p];
-          const float cd = rc.x * g0[p] + rc.y * g1[p] + rc.z * g2[p];
-          const float dLda = use && !(e.raw > kAlphaMax) ? T[p] * cd - RdL[p] * inv : 0.0f;
-          RdL[p] += cd * wgt;
-          x[5] += e.G * dLda;
-          // m = alpha dL/dalpha = -2 dL/dq; the constant factors of the conic and
-          // position gradients are applied once, after the wave's sums (kGradScale)
-          const float m = e.alpha * dLda;
-          x[2] += m * e.dx * e.dx;
-          x[3] += m * e.dx * e.dy;
-          x[4] += m * e.dy * e.dy;
-          x[0] += m * (ra.z * e.dx + hb * e.dy);
-          x[1] += m * (hb * e.dx + rb.x * e.dy);
+          // lanes that do not composite this splat are left out through the exec
+          // mask, or with one block add exact zeros (fewer waves' work to hide
+          // a branch behind)
+          const bool in = lane_in(use);
+          if (PPT == 1 || in) {
+            const float inv = __builtin_amdgcn_rcpf(1.0f - e.alpha);
+            T[p] = PPT > 1 || in ? T[p] * inv : T[p];  // transmittance in front of this splat
+            const float wgt = PPT > 1 || in ? e.alpha * T[p] : 0.0f;
+            x[6] += wgt * g0[p];
+            x[7] += wgt * g1[p];
+            x[8] += wgt * g2[p];
+            const float cd = rc.x * g0[p] + rc.y * g1[p] + rc.z * g2[p];
+            const float dLda = (PPT > 1 || in) && !(e.raw > kAlphaMax) ? T[p] * cd - RdL[p] * inv : 0.0f;
+            RdL[p] += cd * wgt;
+            x[5] += e.G * dLda;
+            // m = alpha dL/dalpha = -2 dL/dq; what does not depend on the pixel (the
+            // conic in the position gradient, the constant factors) is applied
+            // once, to the sums
+            const float m = e.alpha * dLda;
+            const float mdx = m * e.dx, mdy = m * e.dy;
+            x[0] += mdx;
+            x[1] += mdy;
+            x[2] += mdx * e.dx;
+            x[3] += mdx * e.dy;
+            x[4] += mdy * e.dy;
+          }
         }
-        if (__ballot(any) != 0) {  // wave-uniform: the whole wave takes part
+        if (any != 0) {  // wave-uniform: the whole wave takes part
           const float v = reduce_scatter9(x, b2, b3);
           if (writer) s_part[(wave * batch + j) * GS_GRAD_FLOATS + my_e] = v * escale;
         }
@@ -1020,8 +1100,16 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
     // fixed-order sum over the waves, one store per (pair, attribute)
     for (int i = threadIdx.x; i < cnt * GS_GRAD_FLOATS; i += nthreads) {
       const int j = i / GS_GRAD_FLOATS, k = i - j * GS_GRAD_FLOATS;
-      float v = s_part[j * GS_GRAD_FLOATS + k];
-      for (int w = 1; w < nwaves; ++w) v += s_part[(w * batch + j) * GS_GRAD_FLOATS + k];
+      auto total = [&](int e) {
+        float t = s_part[j * GS_GRAD_FLOATS + e];
+        for (int w = 1; w < nwaves; ++w) t += s_part[(w * batch + j) * GS_GRAD_FLOATS + e];
+        return t;
+      };
+      float v = total(k);
+      if (k < 2) {  // sums of m dx and m dy -> position gradient: (a, b/2; b/2, c) of the staged conic
+        const float t = total(1 - k), hb = 0.5f * s_a[j].w;
+        v = k == 0 ? s_a[j].z * v + hb * t : hb * t + s_b[j].x * v;
+      }
       grad_pair[(size_t)s_e[j] * GS_GRAD_FLOATS + k] = v;
       if (k == 0) a.pair_live[s_e[j]] = 1;
     }
