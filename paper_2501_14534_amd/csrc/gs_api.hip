@@ -272,12 +272,15 @@ bool binning_ok(const gs_binning* b, int64_t nrec) {
   return true;
 }
 
-// Backward workspace: per-pair gradients [capacity][9] floats, the per-record
-// planes [kRecPlanes][round_up(V*n, 64)] floats, then one byte per pair (row
-// written this step), padded so that whole words can be read past the end.
+// Backward workspace: per-pair gradients [capacity][9] floats, per view and 64
+// Gaussians a region of 64 x 12 floats (the packed record gradients) and a
+// 64-bit mask, then one byte per pair (row written this step), padded so that
+// whole words can be read past the end.
 size_t grad_pair_bytes(uint64_t capacity) { return align256(sizeof(float) * GS_GRAD_FLOATS * (size_t)capacity); }
-int64_t rec_stride(int64_t nrec) { return (nrec + 63) / 64 * 64; }
-size_t rec_bytes(int64_t nrec) { return sizeof(float) * kRecPlanes * (size_t)rec_stride(nrec); }
+// V views of ceil(n / 64) waves each: at most this many regions for V n records
+size_t rec_regions(int64_t nrec) { return (size_t)nrec / 64 + GS_MAX_VIEWS; }
+size_t rec_region_bytes(int64_t nrec) { return align256(sizeof(float) * 12 * 64 * rec_regions(nrec)); }
+size_t rec_bytes(int64_t nrec) { return rec_region_bytes(nrec) + align256(sizeof(uint64_t) * rec_regions(nrec)); }
 size_t live_bytes(uint64_t capacity) { return align256((size_t)capacity + 256); }
 size_t bwd_ws_bytes(uint64_t capacity, int64_t nrec) {
   return grad_pair_bytes(capacity) + rec_bytes(nrec) + live_bytes(capacity);
@@ -327,7 +330,8 @@ ProjectBwdArgs project_bwd_args(ProjectArgs pa, const gs_opts* opts, const gs_pr
   b.p = pa;
   b.grad_pair = grad_pair;
   b.rec = (float*)((char*)ws + grad_pair_bytes(bins->capacity));
-  b.rec_stride = rec_stride(nrec);
+  b.rec_mask = (uint64_t*)((char*)b.rec + rec_region_bytes(nrec));
+  b.nwaves = (pa.n + 63) / 64;
   b.pair_live = pair_live_ptr(ws, bins->capacity, nrec);
   b.tiles_touched = proj->tiles_touched;
   b.offsets = bins->offsets;

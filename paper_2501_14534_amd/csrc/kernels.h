@@ -80,8 +80,6 @@ struct BinOut {
   int32_t* status;
 };
 
-constexpr int kRecPlanes = 9;
-
 struct ProjectBwdArgs {
   ProjectArgs p;                   // forward inputs (outputs unused)
   const float* grad_pair;          // [K][9], emission order
@@ -89,9 +87,9 @@ struct ProjectBwdArgs {
   const uint32_t* offsets;         // [V*n] first emission position of each record
   const uint8_t* pair_live;        // [K] 1 where the walk wrote the pair's row (others count as zero)
   const int32_t* status;
-  float* rec;                      // [kRecPlanes][rec_stride] per record: sums of the (u, v, A, B, C, o')
-                                   // gradients, then the colour term of the mean gradient
-  int64_t rec_stride;              // V*n rounded up to 64
+  float* rec;                      // [V][nwaves][64][12] packed record gradients of 64 Gaussians
+  uint64_t* rec_mask;              // [V][nwaves] the lanes that are packed
+  int64_t nwaves;                  // n / 64, rounded up
   float* g_means;
   float* g_log_scales;
   float* g_quats;

@@ -3,24 +3,31 @@
 // call and added (+=) to the caller's gradient arrays.  Straight-through
 // estimator for the hard masks (Eq. 3, Eq. 5): d(mask)/d(logit) = sigmoid'.
 //
-// Two kernels (no atomics):
-//   colour:   one thread per Gaussian, the views in order: first its record's
-//             pair gradients summed in emission order (double, rounded once to
-//             float; a wave's records in one view own one contiguous run of
-//             pairs, staged through LDS), then the SH chain in single
-//             precision (diffuse colour, band-mask logits, bands 1..3 when that
-//             gradient is asked for, and the view-direction term of the mean);
-//             the record sums and the colour term go to per-record planes;
-//   geometry: one thread per Gaussian, reading those planes: the EWA chain
-//             in double precision (the 2x2 inverse amplifies rounding by the
-//             condition number of Sigma'):
+// Three kernels (no atomics):
+//   sums:     one wave per 64 consecutive Gaussians and view: each record's pair
+//             gradients summed in emission order (double, rounded once to float;
+//             the records of a wave own one contiguous run of pairs, whose
+//             live rows are staged through LDS); the records with a gradient
+//             are packed, with a mask of their lanes (see `slot`);
+//   colour:   one thread per Gaussian, the views in order: the SH chain in
+//             single precision (diffuse colour, band-mask logits, bands 1..3
+//             when that gradient is asked for, and the view-direction term of
+//             the mean, left in the record's slot);
+//   geometry: one thread per packed record, so that lanes are not idle for the
+//             records without a gradient: the EWA chain in double precision (the
+//             2x2 inverse amplifies rounding by the condition number of Sigma'):
 //     dL/dSigma'  = -Q G_Q Q              (G_Q = [[gA, gB/2], [gB/2, gC]], Q = conic)
 //     dL/dSigma   = T^T dL/dSigma' T,     dL/dT = 2 dL/dSigma' T Sigma,  T = J W
 //     dL/dJ -> camera-space mean (J's entries, the clamp of the lateral ratios),
 //     plus the screen mean (u, v); dL/dmu = W^T dL/dt + colour term;
 //     dL/dM = 2 dL/dSigma M with M = Rq diag(s) -> scales, rotation, through
 //     the quaternion normalisation; opacity and volume mask.
-// Each view's contribution is rounded to float and added to the running
+// Measured at 1M Gaussians in eight views (14.1M pairs, 2.8M live): 95 + 128 +
+// 49 us, 441 us when the colour kernel summed every row of a run and wrote planes
+// of all records; at 6M Gaussians in eight views 490 + 670 + 238 us, 2.30 ms
+// before.  The colour kernel then moves its parameters and gradients at 3.8 TB/s
+// (a large copy reaches 4.8).
+// Each view's contribution is rounded to float and added to the Gaussian's
 // totals in view order with non-contracted adds: the association a sequence
 // of per-view calls produces, so a batched call equals the per-view calls.
 #include "gs_common.h"
@@ -86,75 +93,160 @@ __device__ __forceinline__ float acc_mul_add(float t, float a, float b) {
   return t + p;
 }
 
+// Inclusive prefix sums over the 64 lanes (row shifts by 1, 2, 4, 8, then the
+// rows' totals by broadcasts).
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);
+  return v;
+}
+
 // Sums of the 9 pair gradients of each lane's record (cnt pairs from pair
 // index off; cnt = 0 gives zeros), accumulated in double and rounded once to
 // float.  Called by all 64 lanes of a wave together, for records of
 // consecutive Gaussians in one view: their pairs form one contiguous run of
 // the [K][9] array (emission order is record order).  A pair the backward walk
 // did not reach has no row this step (its live byte is 0) and counts as zero.
-//  - Light records (at most kHeavyPairs pairs): the wave copies the run into
-//    LDS window by window with 16-byte loads of consecutive addresses, with the
-//    pairs' live bytes, and each lane adds its own pairs from LDS in emission
-//    order.  (Loading its pairs directly would touch a separate cache line per
-//    lane and load.)  Windows holding no light record's pairs are skipped.
+//  - Light records (at most kHeavyPairs pairs): window by window of the run, the
+//    wave lists the live pairs (their bytes come in one word per lane, a prefix
+//    sum over the lanes gives each its place) and loads those rows alone into
+//    LDS, three lanes a row.  (Loading its pairs directly would touch a separate
+//    cache line per lane and load; four in five pairs of a dense scene are
+//    dead, and copying their rows too was half of the reads.)  A record's rows
+//    are consecutive there and added in emission order: the first few by the
+//    record's own lane, the rest of a longer record by one lane per component
+//    (the wave would wait for its longest record's lane otherwise).  Windows
+//    holding no light record's pairs are skipped.
 //  - Heavy records (the nearest Gaussians cover thousands of tiles, which one
-//    lane would add up alone) are summed beforehand by heavy_sums_kernel, the
-//    whole wave on one record, and are left at zero here.
+//    lane would add up alone) are left at zero here: the whole wave sums each
+//    of them (heavy_sum).
 // Both orders depend only on the record's own pairs, not on where its run
 // starts, so a record's sums are the same in a batched and a per-view call.
-constexpr int kSumWindow = 256;  // pairs per window (9 x 256 floats = 576 float4, 9 per lane)
+constexpr int kSumWindow = 256;  // pairs per window, four per lane
+constexpr int kSumRows = 96;     // rows in LDS at a time: 26 KB a workgroup, six workgroups per CU
+constexpr int kSumLong = 14;     // records finished by component at a time: two tasks a lane
 constexpr uint32_t kHeavyPairs = 256;
+constexpr uint32_t kDirectRows = 6;
 
-__device__ __forceinline__ void record_sums(const float* __restrict__ grad_pair, const uint8_t* __restrict__ live,
-                                            uint32_t cnt, uint32_t off, float4* win4, uint32_t* livew, int lane,
-                                            float out[GS_GRAD_FLOATS]) {
-  double gsum[GS_GRAD_FLOATS] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+template <int ROWS>
+struct SumLds {                                  // per wave
+  float4 row[ROWS * 3];                          // live rows of the window, three floats in each float4
+  uint32_t pre[kWave];                           // per word of live bytes: live pairs before it | its bits << 16
+  uint8_t pair[kSumWindow];                      // live row -> pair of the window
+  uint32_t rec[kWave];                           // records with more rows than a lane adds alone: those rows,
+                                                 // first | end << 16
+  double acc[kSumLong][GS_GRAD_FLOATS];          // running sums of kSumLong of them
+};
+
+// The pairs [x, y) of the wave's light records (x = y: none).  Offsets grow with
+// the lane (consecutive records), so they lie between the first light lane's
+// start and the last one's end.
+__device__ __forceinline__ uint2 light_run(uint32_t cnt, uint32_t off) {
   const uint32_t lcnt = cnt > kHeavyPairs ? 0u : cnt;
-  // offsets grow with the lane (consecutive records), so the light records'
-  // pairs lie between the first light lane's start and the last one's end
   const uint64_t act = __ballot(lcnt != 0u);
-  const uint32_t lo = act ? (uint32_t)__builtin_amdgcn_readlane((int)off, __builtin_ctzll(act)) : 0u;
-  const uint32_t hi = act ? (uint32_t)__builtin_amdgcn_readlane((int)(off + lcnt), 63 - __builtin_clzll(act)) : 0u;
-  float* win = (float*)win4;
-  uint32_t w0 = lo & ~3u;  // windows start on 16 bytes
-  while (w0 < hi) {
+  if (act == 0) return make_uint2(0u, 0u);
+  return make_uint2((uint32_t)__builtin_amdgcn_readlane((int)off, __builtin_ctzll(act)),
+                    (uint32_t)__builtin_amdgcn_readlane((int)(off + lcnt), 63 - __builtin_clzll(act)));
+}
+
+// Live bytes of pairs w0 + 4 lane .. + 3 (w0 a multiple of 4; the array is padded
+// past the last pair), for the lanes whose word starts before hi.
+__device__ __forceinline__ uint32_t live_word(const uint8_t* __restrict__ live, uint32_t w0, uint32_t hi, int lane) {
+  return w0 + 4u * (uint32_t)lane < hi ? *(const uint32_t*)(live + w0 + 4 * lane) : 0u;
+}
+
+// `run`: light_run(cnt, off); `word`: live_word of its first window, loaded ahead by the caller.
+template <int ROWS>
+__device__ __forceinline__ void record_sums(const float* __restrict__ grad_pair, const uint8_t* __restrict__ live,
+                                            uint32_t cnt, uint32_t off, uint2 run, uint32_t word, SumLds<ROWS>& s,
+                                            int lane, float out[GS_GRAD_FLOATS]) {
+  double sum[GS_GRAD_FLOATS] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+  const uint32_t lcnt = cnt > kHeavyPairs ? 0u : cnt;
+  const uint32_t lo = run.x & ~3u, hi = run.y;  // windows start on whole words of live bytes
+  for (uint32_t w0 = lo; w0 < hi; w0 += kSumWindow) {
     const uint32_t w1 = min(w0 + (uint32_t)kSumWindow, hi);
-    if (__ballot(lcnt != 0u && off < w1 && off + lcnt > w0) == 0) {  // only heavy records' pairs here
-      w0 += kSumWindow;
-      continue;
-    }
-    const int nfl = (int)(w1 - w0) * GS_GRAD_FLOATS, nf4 = nfl / 4;
-    const float* src = grad_pair + (size_t)w0 * GS_GRAD_FLOATS;
-    // loads straight into LDS, no registers in between: lane l of load j
-    // fills float4 64 j + l (lanes past the window are masked off), then
-    // lanes 0 .. nfl % 4 - 1 the floats after the last whole float4
-    constexpr int kPerLane = kSumWindow * GS_GRAD_FLOATS / 4 / kWave;
+    if (__ballot(lcnt != 0u && off < w1 && off + lcnt > w0) == 0) continue;  // only heavy records' pairs here
+    if (w0 != lo) word = live_word(live, w0, hi, lane);
+    uint32_t bits = (word & 1u) | ((word >> 7) & 2u) | ((word >> 14) & 4u) | ((word >> 21) & 8u);
+    const int left = (int)(w1 - w0) - 4 * lane;  // pairs of this lane's word inside the window
+    if (left < 4) bits &= left > 0 ? (1u << left) - 1u : 0u;
+    const uint32_t incl = wave_inclusive_sum((uint32_t)__builtin_popcount(bits));
+    const uint32_t nl = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+    if (nl == 0) continue;  // uniform: no live pair in the window
+    uint32_t at = incl - (uint32_t)__builtin_popcount(bits);
+    s.pre[lane] = at | (bits << 16);
 #pragma unroll
-    for (int j = 0; j < kPerLane; ++j)
-      if (lane + j * kWave < nf4)
-        __builtin_amdgcn_global_load_lds((const void*)((const float4*)src + lane + j * kWave),
-                                         (__attribute__((address_space(3))) void*)(win4 + j * kWave), 16, 0, 0);
-    if (lane < nfl % 4)
-      __builtin_amdgcn_global_load_lds((const void*)(src + nf4 * 4 + lane),
-                                       (__attribute__((address_space(3))) void*)(win + nf4 * 4), 4, 0, 0);
-    // the pairs' live bytes, a word per lane (w0 is a multiple of 4; the array
-    // is padded past the last pair)
-    if (lane < (int)(w1 - w0 + 3) / 4)
-      __builtin_amdgcn_global_load_lds((const void*)(live + w0 + 4 * lane),
-                                       (__attribute__((address_space(3))) void*)livew, 4, 0, 0);
-    __builtin_amdgcn_s_waitcnt(0);  // the LDS writes of the loads above have landed
+    for (int k = 0; k < 4; ++k)
+      if ((bits >> k) & 1u) s.pair[at++] = (uint8_t)(4 * lane + k);
     wave_lds_sync();
-    const uint32_t k1 = min(off + lcnt, w1);
-    const uint8_t* lv = (const uint8_t*)livew;
-    for (uint32_t k = max(off, w0); k < k1; ++k)
-      if (lv[k - w0])  // rows of pairs the walk did not reach are not written: they count as zero
+    uint32_t r0 = 0, r1 = 0;  // this lane's live rows
+    if (lcnt != 0u && off < w1 && off + lcnt > w0) {
+      auto rank = [&](uint32_t k) {  // live pairs of the window before pair k
+        if (k >= (uint32_t)kSumWindow) return nl;
+        const uint32_t q = s.pre[k >> 2];
+        return (q & 0xffffu) + (uint32_t)__builtin_popcount((q >> 16) & ((1u << (k & 3u)) - 1u));
+      };
+      r0 = rank(max(off, w0) - w0);
+      r1 = rank(min(off + lcnt, w1) - w0);
+    }
+    const float* src = grad_pair + (size_t)w0 * GS_GRAD_FLOATS;
+    for (uint32_t rb = 0; rb < nl; rb += ROWS) {  // uniform
+      // rows straight into LDS, no registers in between: three lanes a row, each
+      // 12 bytes into the first three floats of its 16 (the load's lane stride)
+      const uint32_t lanes = 3u * min(nl - rb, (uint32_t)ROWS);
+      for (uint32_t j = 0; j < lanes; j += kWave) {  // uniform
+        const uint32_t e = j + (uint32_t)lane, r = e / 3u;
+        if (e < lanes)
+          __builtin_amdgcn_global_load_lds(
+              (const void*)(src + (uint32_t)s.pair[rb + r] * GS_GRAD_FLOATS + 3u * (e - 3u * r)),
+              (__attribute__((address_space(3))) void*)(s.row + j), 12, 0, 0);
+      }
+      const uint32_t ra = max(r0, rb), re = min(r1, rb + ROWS);
+      const uint32_t rd = min(re, ra + kDirectRows);
+      const uint64_t more = __ballot(rd < re);
+      const uint32_t place = (uint32_t)__popcll(more & ((1ull << lane) - 1ull));
+      if (rd < re) s.rec[place] = (rd - rb) | ((re - rb) << 16);
+      __builtin_amdgcn_s_waitcnt(0);  // the LDS writes of the loads above have landed
+      wave_lds_sync();
+      for (uint32_t r = ra; r < rd; ++r)
 #pragma unroll
-        for (int c = 0; c < GS_GRAD_FLOATS; ++c) gsum[c] += (double)win[(k - w0) * GS_GRAD_FLOATS + c];
-    wave_lds_sync();  // every lane has read the window before the next one overwrites it
-    w0 += kSumWindow;
+        for (int q = 0; q < 3; ++q) {
+          const float4 t = s.row[3 * (r - rb) + q];
+          sum[3 * q + 0] += (double)t.x;
+          sum[3 * q + 1] += (double)t.y;
+          sum[3 * q + 2] += (double)t.z;
+        }
+      const uint32_t nmore = (uint32_t)__popcll(more);
+      for (uint32_t p0 = 0; p0 < nmore; p0 += kSumLong) {  // uniform
+        const bool mine = rd < re && place - p0 < (uint32_t)kSumLong;
+        if (mine)
+#pragma unroll
+          for (int c = 0; c < GS_GRAD_FLOATS; ++c) s.acc[place - p0][c] = sum[c];
+        wave_lds_sync();
+        const uint32_t tasks = GS_GRAD_FLOATS * min(nmore - p0, (uint32_t)kSumLong);
+        for (uint32_t t = (uint32_t)lane; t < tasks; t += kWave) {
+          const uint32_t q = t / GS_GRAD_FLOATS, c = t - q * GS_GRAD_FLOATS, e = s.rec[p0 + q];
+          const float* col = (const float*)s.row + c + c / 3u;  // component c of row 0
+          double x = s.acc[q][c];
+          const uint32_t end = e >> 16;
+#pragma unroll 4
+          for (uint32_t r = e & 0xffffu; r < end; ++r) x += (double)col[12u * r];
+          s.acc[q][c] = x;
+        }
+        wave_lds_sync();
+        if (mine)
+#pragma unroll
+          for (int c = 0; c < GS_GRAD_FLOATS; ++c) sum[c] = s.acc[place - p0][c];
+      }
+      wave_lds_sync();  // every lane has read the rows before the next ones overwrite them
+    }
   }
 #pragma unroll
-  for (int c = 0; c < GS_GRAD_FLOATS; ++c) out[c] = (float)gsum[c];
+  for (int c = 0; c < GS_GRAD_FLOATS; ++c) out[c] = (float)sum[c];
 }
 
 __device__ __forceinline__ double wave_sum_f64(double x) {
@@ -163,39 +255,110 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
   return x;
 }
 
-// Sums of the pair gradients of the heavy records (more than kHeavyPairs
-// pairs), written to the record planes (all nine) for the colour kernel to
-// read.  One thread per record finds them; each wave then takes its heavy
-// records one at a time: lane j adds pairs j, j + 64, ... of the record in
-// double, a butterfly in a fixed pattern adds the lanes, and the sum is
-// rounded once to float.
-__global__ __launch_bounds__(256) void heavy_sums_kernel(ProjectBwdArgs b, int64_t nrec) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int lane = threadIdx.x & (kWave - 1);
-  const uint32_t cnt = r < nrec && *b.status == 0 ? b.tiles_touched[r] : 0u;
-  uint64_t hv = __ballot(cnt > kHeavyPairs);
-  while (hv) {
-    const int L = __builtin_ctzll(hv);
-    hv &= hv - 1;
-    const int64_t hr = (int64_t)__builtin_amdgcn_readlane((int)(r - (int64_t)blockIdx.x * blockDim.x), L) +
-                       (int64_t)blockIdx.x * blockDim.x;
-    const uint32_t hcnt = (uint32_t)__builtin_amdgcn_readlane((int)cnt, L);
-    const uint32_t hoff = b.offsets[hr];
-    double part[GS_GRAD_FLOATS] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    for (uint32_t j = (uint32_t)lane; j < hcnt; j += kWave) {
-      const size_t k = (size_t)hoff + j;
-      if (b.pair_live[k]) {
-        const float* row = b.grad_pair + k * GS_GRAD_FLOATS;
+// The nine sums of one heavy record (cnt pairs from pair index off), by the
+// whole wave: lane j adds pairs j, j + 64, ... in double, a butterfly in a fixed
+// pattern adds the lanes, and the sum is rounded once to float.
+__device__ __forceinline__ void heavy_sum(const float* __restrict__ grad_pair, const uint8_t* __restrict__ live,
+                                          uint32_t cnt, uint32_t off, int lane, float out[GS_GRAD_FLOATS]) {
+  double part[GS_GRAD_FLOATS] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+  for (uint32_t j = (uint32_t)lane; j < cnt; j += kWave) {
+    const size_t k = (size_t)off + j;
+    if (live[k]) {
+      const float* row = grad_pair + k * GS_GRAD_FLOATS;
 #pragma unroll
-        for (int c = 0; c < GS_GRAD_FLOATS; ++c) part[c] += (double)row[c];
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < GS_GRAD_FLOATS; ++c) {
-      const double t = wave_sum_f64(part[c]);
-      if (lane == L) b.rec[c * b.rec_stride + hr] = (float)t;
+      for (int c = 0; c < GS_GRAD_FLOATS; ++c) part[c] += (double)row[c];
     }
   }
+#pragma unroll
+  for (int c = 0; c < GS_GRAD_FLOATS; ++c) out[c] = (float)wave_sum_f64(part[c]);
+}
+
+// What the kernels hand to each other: the nine sums of a record (u, v, A, B, C,
+// o', r, g, b), the last three replaced by the colour term of its mean gradient.
+// The 64 records of a wave's Gaussians in one view own 64 slots of 12 floats;
+// the records with any non-zero sum take them in lane order, in whole 128-byte
+// lines, and rec_mask says which lanes they are.  Most records of a dense scene
+// have no gradient (one in ten has at 1M Gaussians in eight views): planes of
+// all records, zeros included so that lines are written whole, moved 288 MB
+// there each way, the slots about a seventh.
+constexpr int kSlot = 12;
+__device__ __forceinline__ float* slot(const ProjectBwdArgs& b, int v, int64_t wave, int rank) {
+  return b.rec + (((size_t)v * (size_t)b.nwaves + (size_t)wave) * kWave + (size_t)rank) * kSlot;
+}
+__device__ __forceinline__ int rank_of(uint64_t mask, int lane) { return __popcll(mask & ((1ull << lane) - 1ull)); }
+
+// Record sums, one wave per 64 Gaussians and kSumViews views (blockIdx.y).
+// Bound by latency: a wave's counts, live bytes and rows are loads that wait for
+// each other, a few hundred bytes each, so the counts and the live bytes of its
+// views are loaded together where there are waves enough to fill the chip.
+template <int kSumViews, int ROWS>
+__device__ __forceinline__ void sums_of_wave(const ProjectBwdArgs& b, int V, int v0, int64_t gwave, SumLds<ROWS>& lds) {
+  const int64_t n = b.p.n;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t i = gwave * kWave + lane;
+  uint32_t cnts[kSumViews], offs[kSumViews], words[kSumViews];
+#pragma unroll
+  for (int k = 0; k < kSumViews; ++k) {
+    const int64_t r = (int64_t)(v0 + k) * n + i;
+    const bool use = i < n && v0 + k < V;
+    cnts[k] = use ? b.tiles_touched[r] : 0u;
+    offs[k] = use ? b.offsets[r] : 0u;
+  }
+  if (*b.status != 0) {  // overflow: no lists, no gradients
+#pragma unroll
+    for (int k = 0; k < kSumViews; ++k) cnts[k] = 0u;
+  }
+  uint2 runs[kSumViews];
+#pragma unroll
+  for (int k = 0; k < kSumViews; ++k) {
+    runs[k] = light_run(cnts[k], offs[k]);
+    words[k] = live_word(b.pair_live, runs[k].x & ~3u, runs[k].y, lane);
+  }
+#pragma unroll
+  for (int k = 0; k < kSumViews; ++k) {
+    const int v = v0 + k;
+    if (v >= V) break;
+    const uint32_t cnt = cnts[k], off = offs[k];
+    uint64_t mask = 0;
+    if (__ballot(cnt != 0u) != 0) {
+      float g9[GS_GRAD_FLOATS];
+      record_sums(b.grad_pair, b.pair_live, cnt, off, runs[k], words[k], lds, lane, g9);
+      for (uint64_t hv = __ballot(cnt > kHeavyPairs); hv; hv &= hv - 1) {
+        const int L = __builtin_ctzll(hv);
+        float t[GS_GRAD_FLOATS];
+        heavy_sum(b.grad_pair, b.pair_live, (uint32_t)__builtin_amdgcn_readlane((int)cnt, L),
+                  (uint32_t)__builtin_amdgcn_readlane((int)off, L), lane, t);
+#pragma unroll
+        for (int c = 0; c < GS_GRAD_FLOATS; ++c) g9[c] = lane == L ? t[c] : g9[c];
+      }
+      bool some = false;  // a NaN counts
+#pragma unroll
+      for (int c = 0; c < GS_GRAD_FLOATS; ++c) some |= g9[c] != 0.f;
+      if (b.g_mean2d && some) {
+        b.g_mean2d[((int64_t)v * 2 + 0) * n + i] += g9[0];
+        b.g_mean2d[((int64_t)v * 2 + 1) * n + i] += g9[1];
+      }
+      mask = __ballot(some);
+      float* base = slot(b, v, gwave, 0);
+      if (some) {
+        float4* o = (float4*)(base + rank_of(mask, lane) * kSlot);
+        o[0] = make_float4(g9[0], g9[1], g9[2], g9[3]);
+        o[1] = make_float4(g9[4], g9[5], g9[6], g9[7]);
+        o[2] = make_float4(g9[8], 0.f, 0.f, 0.f);
+      }
+      const int used = kSlot * __popcll(mask), pad = -used & 31;  // to the end of the 128-byte line
+      if (lane < pad) base[used + lane] = 0.f;
+    }
+    if (lane == 0) b.rec_mask[(size_t)v * b.nwaves + gwave] = mask;
+  }
+}
+
+template <int kSumViews>
+__global__ __launch_bounds__(256) void project_bwd_sums_kernel(ProjectBwdArgs b, int V) {
+  __shared__ SumLds<kSumRows> s_sum[256 / kWave];
+  const int wave = threadIdx.x / kWave;
+  const int64_t gwave = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave;
+  if (gwave < b.nwaves) sums_of_wave<kSumViews>(b, V, (int)blockIdx.y * kSumViews, gwave, s_sum[wave]);
 }
 
 // A parameter gradient: written (assign) or added.
@@ -222,11 +385,9 @@ __device__ __forceinline__ void colour_grads_out(const ProjectBwdArgs& b, int64_
   }
 }
 
-// Views (bit v) in which record (v, i) touches a tile.
-__device__ __forceinline__ uint32_t visible_views(const ProjectBwdArgs& b, int V, int64_t n, int64_t i) {
-  uint32_t vis = 0;
-  for (int v = 0; v < V; ++v) vis |= (b.tiles_touched[(size_t)v * n + i] != 0u ? 1u : 0u) << v;
-  return vis;
+// Masks of the records with a gradient: word v of a wave's (wave-uniform).
+__device__ __forceinline__ uint64_t record_mask(const ProjectBwdArgs& b, int v, int64_t gwave) {
+  return b.rec_mask[(size_t)v * (size_t)b.nwaves + (size_t)gwave];
 }
 
 // Band masks of Gaussian i (Eq. 5): sigmoid(m_l) > eps <=> m_l > logit(eps).
@@ -250,23 +411,21 @@ __device__ __forceinline__ void view_dir(const ViewArgs& c, const float mu[3], f
   *dx = d0 * *il, *dy = d1 * *il, *dz = d2 * *il;
 }
 
-// Per Gaussian over the views: the record sums of each visible view
-// (record_sums), then the colour chain: the gradient of the clamped colour,
-// the diffuse colour and band-mask gradients, with REST the SH bands 1..DEG
-// (sum over the views of Y_k(d_v) times that gradient; bands whose hard mask
-// is off get nothing), and the colour term of the mean gradient (through the
-// view direction).  Every lane of a wave writes its record's planes in each
-// view the wave visits (zeros where the Gaussian is not visible), so the
-// record planes are written in whole cache lines.
+// Per Gaussian over the views with a gradient: the colour chain: the gradient
+// of the clamped colour, the diffuse colour and band-mask gradients, with REST
+// the SH bands 1..DEG (sum over the views of Y_k(d_v) times that gradient; bands
+// whose hard mask is off get nothing), and the colour term of the mean gradient
+// (through the view direction).
 template <int DEG, bool REST>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void project_bwd_color_kernel(
-    ProjectBwdArgs b, ViewTable vt) {
-  __shared__ float4 s_win[256 / kWave][kSumWindow * GS_GRAD_FLOATS / 4];
-  __shared__ uint32_t s_live[256 / kWave][kSumWindow / 4];
+__device__ __forceinline__ void colour_of_wave(const ProjectBwdArgs& b, const ViewTable& vt) {
   const ProjectArgs& a = b.p;
   const int64_t n = a.n;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int lane = threadIdx.x & (kWave - 1);
+  // the wave of Gaussians, in a scalar register: masks are scalar loads
+  const int64_t gwave = (int64_t)blockIdx.x * (blockDim.x / kWave) +
+                        __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  if (gwave >= b.nwaves) return;
   const bool valid = i < n;
   const int V = vt.nviews;
   constexpr int NRT = REST ? (DEG + 1) * (DEG + 1) - 1 : 1;
@@ -274,13 +433,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void p
   float trest[NRT][3];
 #pragma unroll
   for (int k = 0; k < NRT; ++k) trest[k][0] = trest[k][1] = trest[k][2] = 0.f;
-  // binning overflowed (no lists, no gradients), or the whole wave culled or
-  // off-screen everywhere: zeros when the gradients are written, else nothing
-  const uint32_t vis = valid && *b.status == 0 ? visible_views(b, V, n, i) : 0u;
-  if (__ballot(vis != 0u) == 0) {
+  // no gradient in the whole wave (culled, off-screen, not reached, or the
+  // binning overflowed): zeros when the gradients are written, else nothing
+  uint64_t any = 0;
+  for (int v = 0; v < V; ++v) any |= record_mask(b, v, gwave);
+  if (any == 0) {
     if (b.assign && valid) colour_grads_out<DEG, REST>(b, n, i, zero3, zero3, trest);
     return;
   }
+  const bool vis = (any >> lane) & 1ull;
 
   constexpr int NR = DEG > 0 ? (DEG + 1) * (DEG + 1) - 1 : 1;
   float mu[3] = {0.f, 0.f, 0.f}, dc[3] = {0.f, 0.f, 0.f};
@@ -307,33 +468,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void p
   }
   float tdc[3] = {0.f, 0.f, 0.f}, tbm[3] = {0.f, 0.f, 0.f};
 
-  // v is the same in every lane: camera constants are scalar loads, and a
-  // wave's records in view v are consecutive
-  // (the next view's pair counts and offsets load while this view is processed)
-  uint32_t cnt_next = (vis & 1u) ? b.tiles_touched[i] : 0u, off_next = (vis & 1u) ? b.offsets[i] : 0u;
+  // v is the same in every lane: camera constants are scalar loads
   for (int v = 0; v < V; ++v) {
-    const bool on = (vis >> v) & 1u;
-    const int64_t r = (int64_t)v * n + i;
-    const uint32_t cnt = cnt_next, off = off_next;
-    if (v + 1 < V) {
-      const bool on1 = (vis >> (v + 1)) & 1u;
-      cnt_next = on1 ? b.tiles_touched[r + n] : 0u;
-      off_next = on1 ? b.offsets[r + n] : 0u;
-    }
-    if (__ballot(on) == 0) continue;
-    float g9[GS_GRAD_FLOATS];
-    record_sums(b.grad_pair, b.pair_live, cnt, off, s_win[wave], s_live[wave], lane, g9);
-    if (cnt > kHeavyPairs) {  // summed by heavy_sums_kernel
-#pragma unroll
-      for (int c = 0; c < GS_GRAD_FLOATS; ++c) g9[c] = b.rec[c * b.rec_stride + r];
-    }
-    if (b.g_mean2d && on) {
-      b.g_mean2d[(v * 2 + 0) * n + i] += g9[0];
-      b.g_mean2d[(v * 2 + 1) * n + i] += g9[1];
-    }
+    const uint64_t mask = record_mask(b, v, gwave);
+    if (mask == 0) continue;
+    if (!((mask >> lane) & 1ull)) continue;
+    float* rec = slot(b, v, gwave, rank_of(mask, lane));
     float gmu_col[3] = {0.f, 0.f, 0.f};
-    const float grgb[3] = {g9[6], g9[7], g9[8]};
-    if (on && (grgb[0] != 0.f || grgb[1] != 0.f || grgb[2] != 0.f)) {
+    const float grgb[3] = {rec[6], rec[7], rec[8]};
+    if (grgb[0] != 0.f || grgb[1] != 0.f || grgb[2] != 0.f) {
       const ViewArgs& c = vt.v[v];
       float pre[3] = {dc[0], dc[1], dc[2]};
       float Y[15];
@@ -392,46 +535,64 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void p
         }
       }
     }
-    if (valid) {
-      float* rp = b.rec + r;
 #pragma unroll
-      for (int k = 0; k < 6; ++k) rp[k * b.rec_stride] = on ? g9[k] : 0.f;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) rp[(6 + k) * b.rec_stride] = gmu_col[k];
-    }
+    for (int k = 0; k < 3; ++k) rec[6 + k] = gmu_col[k];
   }
 
   if (!valid || (!vis && !b.assign)) return;
   colour_grads_out<DEG, REST>(b, n, i, tdc, tbm, trest);
 }
 
-// Geometry-kernel outputs of Gaussian i (null arrays: zeros).
+template <int DEG, bool REST>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void project_bwd_color_kernel(
+    ProjectBwdArgs b, ViewTable vt) {
+  colour_of_wave<DEG, REST>(b, vt);
+}
+
+// Geometry-kernel outputs of Gaussian i.
 __device__ __forceinline__ void geom_grads_out(const ProjectBwdArgs& b, int64_t n, int64_t i, const float* tmu,
                                                const float* tls, const float* tq, float top, float tmask) {
   const bool as = b.assign != 0;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    if (b.g_means) grad_out(&b.g_means[k * n + i], as, tmu ? tmu[k] : 0.f);
-    if (b.g_log_scales) grad_out(&b.g_log_scales[k * n + i], as, tls ? tls[k] : 0.f);
+    if (b.g_means) grad_out(&b.g_means[k * n + i], as, tmu[k]);
+    if (b.g_log_scales) grad_out(&b.g_log_scales[k * n + i], as, tls[k]);
   }
 #pragma unroll
   for (int k = 0; k < 4; ++k)
-    if (b.g_quats) grad_out(&b.g_quats[k * n + i], as, tq ? tq[k] : 0.f);
+    if (b.g_quats) grad_out(&b.g_quats[k * n + i], as, tq[k]);
   if (b.g_opacity_logits) grad_out(&b.g_opacity_logits[i], as, top);
   if (b.g_mask_logits && b.p.mask_logits) grad_out(&b.g_mask_logits[i], as, tmask);
 }
 
-__global__ __launch_bounds__(256) void project_bwd_geom_kernel(ProjectBwdArgs b, ViewTable vt) {
-  const ProjectArgs& a = b.p;
-  const int64_t n = a.n;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const uint32_t vis = *b.status == 0 ? visible_views(b, vt.nviews, n, i) : 0u;
-  if (!vis) {  // no gradient (culled, off-screen, or the binning overflowed)
-    if (b.assign) geom_grads_out(b, n, i, nullptr, nullptr, nullptr, 0.f, 0.f);
-    return;
+// Lane of the k-th set bit of m (k < popcount).
+__device__ __forceinline__ int select_lane(uint64_t m, int k) {
+  uint32_t x = (uint32_t)m;
+  int base = 0;
+  const int c0 = __popc(x);
+  if (k >= c0) k -= c0, x = (uint32_t)(m >> 32), base = 32;
+#pragma unroll
+  for (int s = 16; s > 0; s >>= 1) {
+    const int c = __popc(x & ((1u << s) - 1u));
+    if (k >= c) k -= c, x >>= s, base += s;
   }
+  return base;
+}
 
+constexpr int kGeomOut = 12;  // mean 3, log-scale 3, quaternion 4, opacity logit, mask logit
+
+// The geometry chain of record (v, i): its contributions to the gradients of
+// Gaussian i, each rounded to float.
+__device__ __forceinline__ void geom_record(const ProjectArgs& a, const ViewArgs& c, int64_t i,
+                                            const float* __restrict__ rp, float out[kGeomOut]) {
+  const int64_t n = a.n;
+  const double gu = rp[0], gv = rp[1], gA = rp[2], gB = rp[3], gC = rp[4], go = rp[5];
+  const float cmu[3] = {rp[6], rp[7], rp[8]};  // colour term of the mean gradient
+#pragma unroll
+  for (int k = 0; k < kGeomOut; ++k) out[k] = 0.f;
+  if (gu == 0.0 && gv == 0.0 && gA == 0.0 && gB == 0.0 && gC == 0.0 && go == 0.0 && cmu[0] == 0.f && cmu[1] == 0.f &&
+      cmu[2] == 0.f)
+    return;
   float mu[3], ls[3], q[4];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -469,20 +630,6 @@ __global__ __launch_bounds__(256) void project_bwd_geom_kernel(ProjectBwdArgs b,
   double sm = 0.0;
   if (a.mask_logits) sm = 1.0 / (1.0 + exp(-(double)a.mask_logits[i]));
 
-  float tmu[3] = {0.f, 0.f, 0.f}, tls[3] = {0.f, 0.f, 0.f}, tq[4] = {0.f, 0.f, 0.f, 0.f};
-  float top = 0.f, tmask = 0.f;
-  // the views in order, v wave-uniform as in the colour kernel
-  const int V = vt.nviews;
-  for (int v = 0; v < V; ++v) {
-    if (!((vis >> v) & 1u)) continue;
-    const float* rp = b.rec + (size_t)v * n + i;
-    const int64_t rs = b.rec_stride;
-    const double gu = rp[0], gv = rp[rs], gA = rp[2 * rs], gB = rp[3 * rs], gC = rp[4 * rs], go = rp[5 * rs];
-    const float cmu[3] = {rp[6 * rs], rp[7 * rs], rp[8 * rs]};  // colour term of the mean gradient
-    if (gu == 0.0 && gv == 0.0 && gA == 0.0 && gB == 0.0 && gC == 0.0 && go == 0.0 && cmu[0] == 0.f &&
-        cmu[1] == 0.f && cmu[2] == 0.f)
-      continue;
-    const ViewArgs& c = vt.v[v];
     const double fx = c.fx, fy = c.fy;
     const double t0 = (double)c.R[0] * mu[0] + (double)c.R[1] * mu[1] + (double)c.R[2] * mu[2] + (double)c.t[0];
     const double t1 = (double)c.R[3] * mu[0] + (double)c.R[4] * mu[1] + (double)c.R[5] * mu[2] + (double)c.t[1];
@@ -572,47 +719,132 @@ __global__ __launch_bounds__(256) void project_bwd_geom_kernel(ProjectBwdArgs b,
     const double gz = 2.0 * (-2.0 * z * gR[0][0] - w * gR[0][1] + x * gR[0][2] + w * gR[1][0] - 2.0 * z * gR[1][1] +
                              y * gR[1][2] + x * gR[2][0] + y * gR[2][1]);
     const double qd = w * gw + x * gx + y * gy + z * gz;
-    // this view's contribution, rounded to float, added in view order
+    // rounded to float; the caller adds the views in order
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       const double gmu = (double)c.R[k] * gt0 + (double)c.R[3 + k] * gt1 + (double)c.R[6 + k] * gt2;
-      tmu[k] = acc_add(tmu[k], (float)(gmu + (double)cmu[k]));
-      tls[k] = acc_add(tls[k], (float)(gsc[k] * s[k]));
+      out[k] = (float)(gmu + (double)cmu[k]);
+      out[3 + k] = (float)(gsc[k] * s[k]);
     }
-    tq[0] = acc_add(tq[0], (float)((gw - w * qd) * iq));
-    tq[1] = acc_add(tq[1], (float)((gx - x * qd) * iq));
-    tq[2] = acc_add(tq[2], (float)((gy - y * qd) * iq));
-    tq[3] = acc_add(tq[3], (float)((gz - z * qd) * iq));
-    top = acc_add(top, (float)(go * op * (1.0 - op)));
+    out[6] = (float)((gw - w * qd) * iq);
+    out[7] = (float)((gx - x * qd) * iq);
+    out[8] = (float)((gy - y * qd) * iq);
+    out[9] = (float)((gz - z * qd) * iq);
+    out[10] = (float)(go * op * (1.0 - op));
     if (a.mask_logits)  // o' = M o, s' = M s (M = 1 here): dL/dM = o dL/do' + sum_k s_k dL/ds'_k
-      tmask = acc_add(tmask, (float)((go * op + gsc[0] * s[0] + gsc[1] * s[1] + gsc[2] * s[2]) * sm * (1.0 - sm)));
-  }
+      out[11] = (float)((go * op + gsc[0] * s[0] + gsc[1] * s[1] + gsc[2] * s[2]) * sm * (1.0 - sm));
+}
 
-  geom_grads_out(b, n, i, tmu, tls, tq, top, tmask);
+// Geometry: a workgroup owns 256 Gaussians and takes their packed records, view
+// by view, 256 at a time, one per thread; the results wait in LDS until each
+// thread has added its own Gaussian's, in view order.  Bound by the double
+// precision chain (some 600 operations a record): one thread per Gaussian, views
+// in turn, ran it with the one lane in ten that had a gradient.
+__device__ __forceinline__ void geometry_of_block(const ProjectBwdArgs& b, const ViewTable& vt) {
+  constexpr int kWaves = 256 / kWave;
+  __shared__ ViewArgs s_view[GS_MAX_VIEWS];
+  __shared__ uint64_t s_mask[GS_MAX_VIEWS * kWaves];      // [view][wave]
+  __shared__ uint32_t s_pre[GS_MAX_VIEWS * kWaves + 1];   // records before them; the total last
+  __shared__ float s_out[256][kGeomOut + 1];
+  static_assert(GS_MAX_VIEWS * kWaves <= kWave, "one wave scans the masks");
+  const ProjectArgs& a = b.p;
+  const int64_t n = a.n;
+  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave, V = vt.nviews;
+  const int64_t w0 = (int64_t)blockIdx.x * kWaves, i = (int64_t)blockIdx.x * 256 + t;
+  if (wave == 0) {
+    const int64_t gw = w0 + lane % kWaves;
+    const uint64_t m = lane < V * kWaves && gw < b.nwaves ? record_mask(b, lane / kWaves, gw) : 0ull;
+    const uint32_t c = (uint32_t)__popcll(m), incl = wave_inclusive_sum(c);
+    s_mask[lane] = m;
+    s_pre[lane] = incl - c;
+    if (lane == kWave - 1) s_pre[kWave] = incl;
+  } else {
+    constexpr int kWords = sizeof(ViewArgs) / 4;
+    for (int q = t - kWave; q < V * kWords; q += 256 - kWave) ((uint32_t*)s_view)[q] = ((const uint32_t*)vt.v)[q];
+  }
+  __syncthreads();
+  const uint32_t total = s_pre[kWave];
+  float sum[kGeomOut];
+#pragma unroll
+  for (int k = 0; k < kGeomOut; ++k) sum[k] = 0.f;
+  bool some = false;
+  for (uint32_t base = 0; base < total; base += 256) {  // uniform
+    const uint32_t r = base + (uint32_t)t;
+    if (r < total) {
+      int q = 0;  // the last (view, wave) whose first record is at or before r
+#pragma unroll
+      for (int s = kWave / 2; s > 0; s >>= 1)
+        if (s_pre[q + s] <= r) q += s;
+      const int rk = (int)(r - s_pre[q]), v = q / kWaves;
+      const int64_t gw = w0 + q % kWaves;
+      float out[kGeomOut];
+      geom_record(a, s_view[v], gw * kWave + select_lane(s_mask[q], rk), slot(b, v, gw, rk), out);
+#pragma unroll
+      for (int k = 0; k < kGeomOut; ++k) s_out[t][k] = out[k];
+    }
+    __syncthreads();
+    for (int v = 0; v < V; ++v) {
+      const uint64_t m = s_mask[v * kWaves + wave];
+      if (!((m >> lane) & 1ull)) continue;
+      const uint32_t at = s_pre[v * kWaves + wave] + (uint32_t)rank_of(m, lane) - base;
+      if (at >= 256u) continue;  // another chunk's
+      some = true;
+#pragma unroll
+      for (int k = 0; k < kGeomOut; ++k) sum[k] = acc_add(sum[k], s_out[at][k]);
+    }
+    __syncthreads();
+  }
+  if (i >= n || (!some && !b.assign)) return;
+  geom_grads_out(b, n, i, sum, sum + 3, sum + 6, sum[10], sum[11]);
+}
+
+__global__ __launch_bounds__(256, 3) void project_bwd_geom_kernel(ProjectBwdArgs b, ViewTable vt) {
+  geometry_of_block(b, vt);
+}
+
+// The three stages in one launch: each works on the slots of the workgroup's
+// own 256 Gaussians.  For one view and no more workgroups than CUs, where a
+// launch costs as much as a stage (2K Gaussians: three kernels of 17 us in
+// all); more views would run one after the other, and more Gaussians want the
+// occupancy that each stage has on its own.
+template <int DEG, bool REST>
+__global__ __launch_bounds__(256) void project_bwd_small_kernel(ProjectBwdArgs b, ViewTable vt) {
+  __shared__ SumLds<kSumWindow> s_sum[256 / kWave];  // a whole window at once
+  const int wave = threadIdx.x / kWave;
+  const int64_t gwave = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave;
+  if (gwave < b.nwaves) sums_of_wave<1>(b, 1, 0, gwave, s_sum[wave]);
+  __syncthreads();
+  colour_of_wave<DEG, REST>(b, vt);
+  __syncthreads();
+  geometry_of_block(b, vt);
+}
+
+template <int DEG, bool REST>
+static void launch_stages(const ProjectBwdArgs& a, const ViewTable& vt, hipStream_t s) {
+  const dim3 block(256), grid((unsigned)((a.p.n + 255) / 256));
+  if (vt.nviews == 1 && grid.x <= 256) {
+    hipLaunchKernelGGL((project_bwd_small_kernel<DEG, REST>), grid, block, 0, s, a, vt);
+    return;
+  }
+  // one view a wave until that gives more than the 4096 waves that run at once
+  if (a.nwaves * vt.nviews > 4 * 4096)
+    hipLaunchKernelGGL(project_bwd_sums_kernel<4>, dim3(grid.x, (unsigned)((vt.nviews + 3) / 4)), block, 0, s, a,
+                       (int)vt.nviews);
+  else
+    hipLaunchKernelGGL(project_bwd_sums_kernel<1>, dim3(grid.x, (unsigned)vt.nviews), block, 0, s, a, (int)vt.nviews);
+  hipLaunchKernelGGL((project_bwd_color_kernel<DEG, REST>), grid, block, 0, s, a, vt);
+  hipLaunchKernelGGL(project_bwd_geom_kernel, grid, block, 0, s, a, vt);
 }
 
 hipError_t launch_project_bwd(const ProjectBwdArgs& a, const ViewTable& vt, int deg, hipStream_t s) {
   if (a.p.n == 0) return hipSuccess;
-  const dim3 block(256), grid((unsigned)((a.p.n + 255) / 256));
-  const int64_t nrec = (int64_t)vt.nviews * a.p.n;
-  hipLaunchKernelGGL(heavy_sums_kernel, dim3((unsigned)((nrec + 255) / 256)), block, 0, s, a, nrec);
   const bool rest = a.g_sh_rest != nullptr && deg > 0;
   switch (deg) {
-    case 0: hipLaunchKernelGGL((project_bwd_color_kernel<0, false>), grid, block, 0, s, a, vt); break;
-    case 1:
-      if (rest) hipLaunchKernelGGL((project_bwd_color_kernel<1, true>), grid, block, 0, s, a, vt);
-      else hipLaunchKernelGGL((project_bwd_color_kernel<1, false>), grid, block, 0, s, a, vt);
-      break;
-    case 2:
-      if (rest) hipLaunchKernelGGL((project_bwd_color_kernel<2, true>), grid, block, 0, s, a, vt);
-      else hipLaunchKernelGGL((project_bwd_color_kernel<2, false>), grid, block, 0, s, a, vt);
-      break;
-    default:
-      if (rest) hipLaunchKernelGGL((project_bwd_color_kernel<3, true>), grid, block, 0, s, a, vt);
-      else hipLaunchKernelGGL((project_bwd_color_kernel<3, false>), grid, block, 0, s, a, vt);
-      break;
+    case 0: launch_stages<0, false>(a, vt, s); break;
+    case 1: rest ? launch_stages<1, true>(a, vt, s) : launch_stages<1, false>(a, vt, s); break;
+    case 2: rest ? launch_stages<2, true>(a, vt, s) : launch_stages<2, false>(a, vt, s); break;
+    default: rest ? launch_stages<3, true>(a, vt, s) : launch_stages<3, false>(a, vt, s); break;
   }
-  hipLaunchKernelGGL(project_bwd_geom_kernel, grid, block, 0, s, a, vt);
   return hipGetLastError();
 }
 
