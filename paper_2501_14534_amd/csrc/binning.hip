@@ -2,7 +2,7 @@
 //
 //   1. count_reduce + scan_top: device-wide exclusive scans of tiles_touched
 //      (the canonical emission offsets, K and the capacity status) and of
-//      the visibility flags (tiles_touched > 0), 1024 records per block.
+//      the visibility flags (tiles_touched > 0), 4096 records per block.
 //   2. compact_visible: writes each record's canonical offset and packs each
 //      visible record as (depth bits, compact index) plus a 16-byte emission
 //      descriptor (first tile, rect width and height, canonical offset, id).
@@ -14,9 +14,9 @@
 //      emit_pairs: the records, now in depth order, emit one (tile, canonical
 //      pair index, record id) per touched tile into a contiguous
 //      depth-ordered range; each workgroup fills a fixed chunk of output
-//      positions slot by slot (binary search of the owning record in LDS), so
-//      writes are coalesced and neither a big Gaussian nor a block of them
-//      serialises the work.
+//      positions slot by slot (the owning records by a running maximum over the
+//      chunk), so writes are coalesced and neither a big Gaussian nor a block
+//      of them serialises the work.
 //   5. LSD radix sort of the pairs by tile id only (ceil(log2 #tiles) bits,
 //      two passes up to 65536 tiles), carrying pair index and record id.
 //      Stability keeps depth order, and record order among equal depths,
@@ -36,9 +36,10 @@ namespace gs {
 
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 4;
-constexpr int kScanTile = kScanThreads * kScanItems;  // records per scan block
-constexpr int kSortThreads = 256;
-constexpr int kSortItems = 16;
+constexpr int kScanTile = kScanThreads * kScanItems;  // depth-sorted records per emission scan block
+constexpr int kRecTile = 4 * kScanTile;               // records per scan block: four rounds of kScanTile
+constexpr int kSortThreads = 512;
+constexpr int kSortItems = 8;
 constexpr int kSortTile = kSortThreads * kSortItems;  // keys per sort block
 constexpr int kRadix = 256;
 
@@ -81,284 +82,381 @@ __device__ __forceinline__ uint32_t block_exclusive_scan_256(uint32_t x, uint32_
   return incl - x + off;
 }
 
-// Per block of 1024 records: sum of tiles_touched and number of visible records.
-__global__ __launch_bounds__(kScanThreads) void count_reduce(const uint32_t* __restrict__ tt, int64_t len,
-                                                             uint32_t* __restrict__ block_sums,
-                                                             uint32_t* __restrict__ vis_sums) {
-  __shared__ uint32_t s_wave[kScanThreads / kWave];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-  uint32_t s = 0, v = 0;
+// Four consecutive words of an array that is only word-aligned.
+struct __attribute__((packed, aligned(4))) Words4 {
+  uint32_t w[4];
+};
+
+// The caller's four consecutive records of round k of its block (0 past the end).
+__device__ __forceinline__ void load_counts(const uint32_t* __restrict__ tt, int64_t r0, int64_t nrec,
+                                            uint32_t c[kScanItems]) {
+  if (r0 + kScanItems <= nrec) {
+    const Words4 q = *(const Words4*)(tt + r0);
 #pragma unroll
-  for (int k = 0; k < kScanItems; ++k)
-    if (base + k < len) {
-      const uint32_t c = tt[base + k];
-      s += c;
-      v += c != 0u;
-    }
-  uint32_t tot;
-  block_exclusive_scan_256(s, &tot, s_wave);
-  if (threadIdx.x == 0) block_sums[blockIdx.x] = tot;
-  block_exclusive_scan_256(v, &tot, s_wave);
-  if (threadIdx.x == 0) vis_sums[blockIdx.x] = tot;
+    for (int j = 0; j < kScanItems; ++j) c[j] = q.w[j];
+  } else {
+#pragma unroll
+    for (int j = 0; j < kScanItems; ++j) c[j] = r0 + j < nrec ? tt[r0 + j] : 0u;
+  }
 }
 
-// Single block: exclusive scan of nb block sums and their total (64-bit
-// accumulation, saturated to 32 bits).  With a status word: status = 1 when
-// the total exceeds capacity.
-__global__ __launch_bounds__(1024) void scan_top(const uint32_t* __restrict__ sums, int64_t nb,
-                                                 uint32_t* __restrict__ offsets, uint64_t capacity,
-                                                 uint32_t* total_out, int32_t* status) {
-  constexpr int kItems = 8;  // consecutive sums per thread: 8192 per step, one step up to 8M records
-  __shared__ uint32_t s_wave[16];
+// Per block of 4096 records: sum of tiles_touched (saturated to 32 bits, which
+// no capacity holds) and number of visible records.
+__global__ __launch_bounds__(kScanThreads) void count_reduce(const uint32_t* __restrict__ tt, int64_t nrec,
+                                                             uint2* __restrict__ block_sums) {
+  __shared__ unsigned long long s_pairs[kScanThreads / kWave];
+  __shared__ uint32_t s_vis[kScanThreads / kWave];
+  const int64_t base = (int64_t)blockIdx.x * kRecTile + (int64_t)threadIdx.x * kScanItems;
+  unsigned long long s = 0;
+  uint32_t v = 0;
+#pragma unroll
+  for (int k = 0; k < kRecTile / kScanTile; ++k) {
+    uint32_t c[kScanItems];
+    load_counts(tt, base + k * kScanTile, nrec, c);
+#pragma unroll
+    for (int j = 0; j < kScanItems; ++j) {
+      s += c[j];
+      v += c[j] != 0u;
+    }
+  }
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    s += __shfl_xor(s, o, kWave);
+    v += __shfl_xor(v, o, kWave);
+  }
+  if ((threadIdx.x & (kWave - 1)) == 0) s_pairs[threadIdx.x / kWave] = s, s_vis[threadIdx.x / kWave] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int w = 1; w < kScanThreads / kWave; ++w) s += s_pairs[w], v += s_vis[w];
+    block_sums[blockIdx.x] = make_uint2(s > 0xffffffffull ? 0xffffffffu : (uint32_t)s, v);
+  }
+}
+
+// Single block: exclusive scans of nb block sums in place, .x with 64-bit
+// accumulation (the total saturated to 32 bits; with a status word, status = 1
+// when it exceeds capacity), .y too where total_y is given.
+// With a count, only the blocks of 1024 that hold that many entries.
+__global__ __launch_bounds__(1024) void scan_top(uint2* __restrict__ sums, int64_t nb, const uint32_t* count,
+                                                 uint64_t capacity, uint32_t* total_x, uint32_t* total_y,
+                                                 int32_t* status) {
+  constexpr int kItems = 4;  // consecutive sums per thread: 4096 per step, one step up to 16M records
+  __shared__ unsigned long long s_wave[16];
+  __shared__ uint32_t s_wave_y[16];
   __shared__ unsigned long long s_carry;
+  __shared__ uint32_t s_carry_y;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  if (threadIdx.x == 0) s_carry = 0;
+  if (threadIdx.x == 0) s_carry = 0, s_carry_y = 0;
+  if (count) nb = min(nb, ((int64_t)*count + 1023) / 1024);
   __syncthreads();
   for (int64_t base = 0; base < nb; base += kItems * 1024) {
     const int64_t i0 = base + (int64_t)kItems * threadIdx.x;
-    uint32_t x[kItems], sum = 0;
+    uint2 x[kItems];
+    unsigned long long sum = 0;
+    uint32_t sum_y = 0;
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
-      x[j] = i0 + j < nb ? sums[i0 + j] : 0u;
-      sum += x[j];
+      x[j] = i0 + j < nb ? sums[i0 + j] : make_uint2(0u, 0u);
+      sum += x[j].x;
+      sum_y += x[j].y;
     }
-    uint32_t incl = sum;
+    unsigned long long incl = sum;
+    uint32_t incl_y = sum_y;
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
-      const uint32_t y = __shfl_up(incl, o, kWave);
-      if (lane >= o) incl += y;
+      const unsigned long long a = __shfl_up(incl, o, kWave);
+      const uint32_t b = __shfl_up(incl_y, o, kWave);
+      if (lane >= o) incl += a, incl_y += b;
     }
-    if (lane == kWave - 1) s_wave[wave] = incl;
+    if (lane == kWave - 1) s_wave[wave] = incl, s_wave_y[wave] = incl_y;
     __syncthreads();
     unsigned long long off = 0, tot = 0;
+    uint32_t off_y = 0, tot_y = 0;
     for (int w = 0; w < 16; ++w) {
       const unsigned long long c = s_wave[w];
+      const uint32_t cy = s_wave_y[w];
       off += (w < wave) ? c : 0ull;
+      off_y += (w < wave) ? cy : 0u;
       tot += c;
+      tot_y += cy;
     }
     const unsigned long long carry = s_carry;
-    unsigned long long ex = carry + off + incl - sum;
+    const uint32_t carry_y = s_carry_y;
+    uint2 ex = make_uint2((uint32_t)(carry + off + incl - sum), carry_y + off_y + incl_y - sum_y);
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
-      if (i0 + j < nb) offsets[i0 + j] = (uint32_t)ex;
-      ex += x[j];
+      if (i0 + j < nb) sums[i0 + j] = ex;
+      ex.x += x[j].x;
+      ex.y += x[j].y;
     }
     __syncthreads();
-    if (threadIdx.x == 0) s_carry = carry + tot;
+    if (threadIdx.x == 0) s_carry = carry + tot, s_carry_y = carry_y + tot_y;
     __syncthreads();
   }
   if (threadIdx.x == 0) {
     const unsigned long long K = s_carry;
-    *total_out = K > 0xffffffffull ? 0xffffffffu : (uint32_t)K;
+    *total_x = K > 0xffffffffull ? 0xffffffffu : (uint32_t)K;
+    if (total_y) *total_y = s_carry_y;
     if (status) *status = K > (unsigned long long)capacity ? 1 : 0;
   }
-}
-
-// Exclusive scans of two values per thread over a 256-thread block (one pass
-// of barriers for both).
-__device__ __forceinline__ void block_exclusive_scan2_256(uint32_t x, uint32_t y, uint32_t* ex, uint32_t* ey,
-                                                          uint32_t* tx, uint32_t* ty, uint2* s_wave) {
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  uint32_t ix = x, iy = y;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint32_t a = __shfl_up(ix, o, kWave), b = __shfl_up(iy, o, kWave);
-    if (lane >= o) ix += a, iy += b;
-  }
-  if (lane == kWave - 1) s_wave[wave] = make_uint2(ix, iy);
-  __syncthreads();
-  uint32_t ox = 0, oy = 0, sx = 0, sy = 0;
-#pragma unroll
-  for (int w = 0; w < kScanThreads / kWave; ++w) {
-    const uint2 c = s_wave[w];
-    ox += (w < wave) ? c.x : 0u;
-    oy += (w < wave) ? c.y : 0u;
-    sx += c.x;
-    sy += c.y;
-  }
-  __syncthreads();
-  *ex = ix - x + ox;
-  *ey = iy - y + oy;
-  *tx = sx;
-  *ty = sy;
 }
 
 // Canonical emission offsets of every record (pairs of record r occupy
 // [offsets[r], offsets[r] + tiles_touched[r]), records in index order), and
 // the visible records packed in record order as (depth bits, compact index)
-// with their emission descriptors; drec[r] = depth bits for the keys.  The
-// block's 1024 records are taken in four slices of 256 consecutive records,
-// one per thread, so loads and stores are coalesced.
+// with their emission descriptors; drec[r] = depth bits for the keys.  Bound by
+// HBM traffic: two words per record, and the lines of the visible records'
+// splats, whose other half is not needed.  A block takes its 4096 records in
+// rounds of 1024, four slices of 256 consecutive ones a round, so loads and
+// stores are coalesced; the slices' wave sums meet at one barrier a round.
+// (Four consecutive records a thread, one 16-byte load and store, read the
+// splats at four times the stride: 103 -> 155 us at 8M records, 4M visible.)
 __global__ __launch_bounds__(kScanThreads) void compact_visible(const float4* __restrict__ splats,
                                                                 const uint32_t* __restrict__ tt, int64_t nrec,
                                                                 int64_t n, ViewTable vt, float inv_tw, float inv_th,
-                                                                const uint32_t* __restrict__ block_offsets,
-                                                                const uint32_t* __restrict__ vis_offsets,
+                                                                const uint2* __restrict__ block_offsets,
                                                                 const int32_t* __restrict__ status,
                                                                 uint32_t* __restrict__ offsets,
                                                                 uint32_t* __restrict__ dkey,
                                                                 uint32_t* __restrict__ dval, uint4* __restrict__ desc,
                                                                 uint32_t* __restrict__ drec) {
-  __shared__ uint2 s_wave[kScanThreads / kWave];
+  constexpr int kWaves = kScanThreads / kWave;
+  __shared__ uint2 s_wave[2][kScanItems * kWaves];  // per slice and wave; two buffers in turn: one barrier a round
   if (*status != 0) return;  // overflow: no lists this step
-  const int64_t blk = (int64_t)blockIdx.x * kScanTile;
-  uint32_t ex_base = block_offsets[blockIdx.x], vx_base = vis_offsets[blockIdx.x];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  uint2 base = block_offsets[blockIdx.x];
+  for (int k = 0; k < kRecTile / kScanTile; ++k) {
+    const int64_t r0 = (int64_t)blockIdx.x * kRecTile + k * kScanTile + threadIdx.x;
+    if (r0 - threadIdx.x >= nrec) break;  // uniform
+    uint32_t c[kScanItems], ex[kScanItems], vx[kScanItems];
 #pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    const int64_t r = blk + k * kScanThreads + threadIdx.x;
-    const uint32_t c = r < nrec ? tt[r] : 0u;
-    uint32_t ex, vx, ts, tv;
-    block_exclusive_scan2_256(c, c != 0u ? 1u : 0u, &ex, &vx, &ts, &tv, s_wave);
-    ex += ex_base;
-    vx += vx_base;
-    ex_base += ts;
-    vx_base += tv;
-    if (r < nrec) offsets[r] = ex;
-    if (c) {
-      const float4 p0 = splats[r * 3 + 0];
-      const float4 p1 = splats[r * 3 + 1];
+    for (int j = 0; j < kScanItems; ++j) c[j] = r0 + j * kScanThreads < nrec ? tt[r0 + j * kScanThreads] : 0u;
+#pragma unroll
+    for (int j = 0; j < kScanItems; ++j) {
+      const uint32_t incl = wave_inclusive_sum(c[j]);
+      const uint64_t vis = __ballot(c[j] != 0u);
+      ex[j] = incl - c[j];
+      vx[j] = (uint32_t)__popcll(vis & ((1ull << lane) - 1ull));
+      if (lane == kWave - 1) s_wave[k & 1][j * kWaves + wave] = make_uint2(incl, (uint32_t)__popcll(vis));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kScanItems; ++j) {
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        if (w == wave) ex[j] += base.x, vx[j] += base.y;
+        const uint2 q = s_wave[k & 1][j * kWaves + w];
+        base.x += q.x;
+        base.y += q.y;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kScanItems; ++j) {
+      const int64_t r = r0 + j * kScanThreads;
+      if (r < nrec) offsets[r] = ex[j];
+      if (c[j] == 0u) continue;
+      const float2 uv = *(const float2*)(splats + r * 3);            // u, v
+      const float2 rd = *((const float2*)(splats + r * 3 + 1) + 1);  // radius, depth
       int v = 0;
       while (v + 1 < vt.nviews && r >= (int64_t)(v + 1) * n) ++v;
       const ViewArgs& va = vt.v[v];
       int x0, y0, x1, y1;
-      tile_rect(p0.x, p0.y, p1.z, inv_tw, inv_th, va.TX, va.TY, &x0, &y0, &x1, &y1);
-      const uint32_t dbits = __float_as_uint(p1.w);  // depth > near plane > 0: bits order as values
-      dkey[vx] = dbits;
-      dval[vx] = vx;
-      desc[vx] = make_uint4((uint32_t)(va.tile_off + y0 * va.TX + x0),
-                            (uint32_t)(x1 - x0 + 1) | ((uint32_t)(y1 - y0 + 1) << 16), ex, (uint32_t)r);
+      tile_rect(uv.x, uv.y, rd.x, inv_tw, inv_th, va.TX, va.TY, &x0, &y0, &x1, &y1);
+      const uint32_t dbits = __float_as_uint(rd.y);  // depth > near plane > 0: bits order as values
+      dkey[vx[j]] = dbits;
+      dval[vx[j]] = vx[j];
+      desc[vx[j]] = make_uint4((uint32_t)(va.tile_off + y0 * va.TX + x0),
+                               (uint32_t)(x1 - x0 + 1) | ((uint32_t)(y1 - y0 + 1) << 16), ex[j], (uint32_t)r);
       if (drec) drec[r] = dbits;
     }
   }
 }
 
 // Per block of 1024 depth-sorted records: their descriptors gathered into
-// depth order (sdesc, read sequentially by emit_pairs) and their number of
-// pairs.
+// depth order, (first tile, rect width | the view's tile columns << 16, first
+// canonical pair, record), their output positions within the block, and the
+// block's number of pairs.  Bound by the gather: 16 bytes of a line a record.
 __global__ __launch_bounds__(kScanThreads) void gather_reduce(const uint4* __restrict__ desc,
                                                               const uint32_t* __restrict__ dval,
                                                               const uint32_t* __restrict__ nvis,
-                                                              const int32_t* __restrict__ status,
-                                                              uint4* __restrict__ sdesc,
-                                                              uint32_t* __restrict__ block_sums) {
-  __shared__ uint32_t s_wave[kScanThreads / kWave];
+                                                              const int32_t* __restrict__ status, ViewTable vt,
+                                                              uint4* __restrict__ sdesc, uint32_t* __restrict__ epref,
+                                                              uint2* __restrict__ block_sums) {
+  constexpr int kWaves = kScanThreads / kWave;
+  __shared__ uint32_t s_wave[kScanItems * kWaves];
   const uint32_t N = effective_count(nvis, status);
   const int64_t blk = (int64_t)blockIdx.x * kScanTile;
-  uint32_t s = 0;
+  if (blk >= N) return;  // uniform: past the sums that are read
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  uint4 d[kScanItems];
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     const int64_t m = blk + k * kScanThreads + threadIdx.x;
+    d[k] = m < N ? desc[dval[m]] : make_uint4(0u, 0u, 0u, 0u);
+  }
+  uint32_t ex[kScanItems];
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    const uint32_t c = (d[k].y & 0xffffu) * (d[k].y >> 16), incl = wave_inclusive_sum(c);
+    ex[k] = incl - c;
+    if (lane == kWave - 1) s_wave[k * kWaves + wave] = incl;
+  }
+  __syncthreads();
+  uint32_t run = 0;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      if (w == wave) ex[k] += run;
+      run += s_wave[k * kWaves + w];
+    }
+    const int64_t m = blk + k * kScanThreads + threadIdx.x;
     if (m < N) {
-      const uint4 d = desc[dval[m]];
-      sdesc[m] = d;
-      s += (d.y & 0xffffu) * (d.y >> 16);
+      int v = 0;  // view of the record's first tile
+      while (v + 1 < vt.nviews && d[k].x >= (uint32_t)vt.v[v + 1].tile_off) ++v;
+      sdesc[m] = make_uint4(d[k].x, (d[k].y & 0xffffu) | ((uint32_t)vt.v[v].TX << 16), d[k].z, d[k].w);
+      epref[m] = ex[k];
     }
   }
-  uint32_t tot;
-  block_exclusive_scan_256(s, &tot, s_wave);
-  if (threadIdx.x == 0) block_sums[blockIdx.x] = tot;
+  if (threadIdx.x == 0) block_sums[blockIdx.x] = make_uint2(run, 0u);
 }
 
-// Output positions per emission workgroup.
-constexpr int kEmitChunk = 1536;  // 5 staged words per record: 30 KB of LDS, 5 workgroups per CU
+// Output positions per emission workgroup, 8 per thread: a block of the tile
+// sort, whose first digit's histogram the emission counts as it goes.
+constexpr int kEmitItems = 8;
+constexpr int kEmitThreads = kSortTile / kEmitItems;
+constexpr int kEmitChunk = kSortTile;
 
-// Emission offsets in depth order: epref[m] = the first output position of
-// depth-sorted record m (its block's offset plus the exclusive prefix of the
-// pair counts within the block of 1024), and for every chunk of kEmitChunk
-// output positions the record holding its first position (chunk_first).
-__global__ __launch_bounds__(kScanThreads) void emit_prefix(const uint4* __restrict__ sdesc,
-                                                            const uint32_t* __restrict__ nvis,
-                                                            const uint32_t* __restrict__ eblock_offsets,
+// Emission offsets in depth order: epref[m], the position within its block of
+// 1024, becomes the first output position of depth-sorted record m, and
+// chunk_first of every chunk of kEmitChunk output positions the record holding
+// its first position.
+__global__ __launch_bounds__(kScanThreads) void emit_prefix(const uint32_t* __restrict__ nvis,
+                                                            const uint32_t* __restrict__ count,
+                                                            const uint2* __restrict__ eblock_offsets,
                                                             const int32_t* __restrict__ status,
                                                             uint32_t* __restrict__ epref,
                                                             uint32_t* __restrict__ chunk_first) {
-  __shared__ uint32_t s_wave[kScanThreads / kWave];
   const uint32_t N = effective_count(nvis, status);
   const int64_t blk = (int64_t)blockIdx.x * kScanTile;
   if (blk >= N) return;  // uniform
-  // thread t takes 4 consecutive records, so the block scan runs in record order
+  const uint32_t off = eblock_offsets[blockIdx.x].x;
+  const int64_t next_blk = blk + kScanTile;
+  const uint32_t end = next_blk < N ? eblock_offsets[blockIdx.x + 1].x : *count;  // the block's last position + 1
   const int64_t m0 = blk + (int64_t)threadIdx.x * kScanItems;
-  uint32_t c[kScanItems], sum = 0;
+  uint32_t ex[kScanItems + 1];
+#pragma unroll
+  for (int k = 0; k <= kScanItems; ++k)
+    ex[k] = m0 + k < min((int64_t)N, next_blk) ? off + epref[m0 + k] : end;
+  __syncthreads();  // every position has been read
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
-    c[k] = 0u;
-    if (m0 + k < N) {
-      const uint32_t wh = sdesc[m0 + k].y;
-      c[k] = (wh & 0xffffu) * (wh >> 16);
-    }
-    sum += c[k];
-  }
-  uint32_t total;
-  uint32_t ex = block_exclusive_scan_256(sum, &total, s_wave) + eblock_offsets[blockIdx.x];
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    if (m0 + k < N) {
-      epref[m0 + k] = ex;
-      // chunks whose first position lies in [ex, ex + c)
-      for (uint32_t q = (ex + kEmitChunk - 1) / kEmitChunk; q * (uint64_t)kEmitChunk < (uint64_t)ex + c[k]; ++q)
-        chunk_first[q] = (uint32_t)(m0 + k);
-    }
-    ex += c[k];
+    if (m0 + k >= N) break;
+    epref[m0 + k] = ex[k];
+    // chunks whose first position lies in [ex[k], ex[k + 1])
+    for (uint32_t q = (ex[k] + kEmitChunk - 1) / kEmitChunk; q * (uint64_t)kEmitChunk < (uint64_t)ex[k + 1]; ++q)
+      chunk_first[q] = (uint32_t)(m0 + k);
   }
 }
 
 // Emission in depth order: sorted record m emits, at output positions
 // [epref[m], epref[m] + w h), its tiles in row-major order of its tile
 // rectangle: tile id, the pair's canonical index offsets[r] + j, and r.
-// Workgroup c owns output positions [c C, (c + 1) C), C = kEmitChunk: it
-// stages the descriptors of the records from the one holding its first
-// position to the one holding the next chunk's (at most C + 1: every record
-// has a pair) and fills its slots in order (binary search of the owning
-// record in LDS).  Work per workgroup is bounded by C slots however many
-// pairs one record has (the nearest Gaussians cover thousands of tiles), and
-// consecutive threads write consecutive positions.
-__global__ __launch_bounds__(kScanThreads) void emit_pairs(const uint4* __restrict__ sdesc,
+// Workgroup c owns output positions [c C, (c + 1) C), C = kEmitChunk.  The
+// records from the one holding its first position to the one holding the next
+// chunk's (at most C + 1: every record has a pair) mark the slots where they
+// start; a running maximum over the slots then gives each its record, whose
+// descriptor consecutive threads read from one or two cache lines.  (A binary
+// search of the record in LDS, ten dependent reads a slot over 30 KB of staged
+// descriptors, took 68 us for 14.1M pairs and left the first histogram to a pass
+// of 30 us; now 60 us with it.)  Work per workgroup is bounded by C
+// slots however many pairs one record has (the nearest Gaussians cover
+// thousands of tiles), and consecutive threads write consecutive positions.
+// hist (the tile sort's, nblk columns): column c counts the chunk's tile ids by
+// their low digit.
+__global__ __launch_bounds__(kEmitThreads) void emit_pairs(const uint4* __restrict__ sdesc,
                                                            const uint32_t* __restrict__ epref,
                                                            const uint32_t* __restrict__ chunk_first,
                                                            const uint32_t* __restrict__ nvis,
                                                            const uint32_t* __restrict__ count,
-                                                           const int32_t* __restrict__ status, ViewTable vt,
+                                                           const int32_t* __restrict__ status,
                                                            uint32_t* __restrict__ tkey, uint32_t* __restrict__ tval,
-                                                           uint32_t* __restrict__ trec) {
-  constexpr int kR = kEmitChunk + 1;
-  __shared__ uint32_t s_pref[kR];
-  __shared__ uint32_t s_base[kR];
-  __shared__ uint32_t s_wtx[kR];  // rect width | the view's tile columns << 16
-  __shared__ uint32_t s_rec[kR];
-  __shared__ uint32_t s_off[kR];
+                                                           uint32_t* __restrict__ trec, int64_t nblk,
+                                                           uint32_t* __restrict__ hist) {
+  __shared__ __align__(16) uint16_t s_own[kEmitChunk];  // record that starts at the slot, then the slot's record
+  __shared__ uint32_t s_wave[kEmitThreads / kWave];
+  __shared__ uint32_t s_hist[kRadix];
   const uint32_t N = effective_count(nvis, status);
   const uint32_t K = effective_count(count, status);
-  const uint32_t slot0 = blockIdx.x * (uint32_t)kEmitChunk;
-  if (N == 0 || slot0 >= K) return;  // uniform
-  const uint32_t slot1 = min(slot0 + (uint32_t)kEmitChunk, K);
-  const uint32_t m0 = chunk_first[blockIdx.x];
-  const uint32_t m_end = slot1 < K ? chunk_first[blockIdx.x + 1] + 1u : N;
-  const int nr = (int)(m_end - m0);  // records that may own slots of the chunk (<= kR)
-  for (int i = threadIdx.x; i < nr; i += kScanThreads) {
-    const uint4 d = sdesc[m0 + i];
-    int v = 0;  // view of the record's first tile
-    while (v + 1 < vt.nviews && d.x >= (uint32_t)vt.v[v + 1].tile_off) ++v;
-    s_pref[i] = epref[m0 + i];
-    s_base[i] = d.x;
-    s_wtx[i] = (d.y & 0xffffu) | ((uint32_t)vt.v[v].TX << 16);
-    s_off[i] = d.z;
-    s_rec[i] = d.w;
+  const int64_t nact = ((int64_t)K + kEmitChunk - 1) / kEmitChunk;
+  if (N == 0 || (int64_t)blockIdx.x >= nact) return;  // uniform
+  const int64_t blk = xcd_block((int64_t)blockIdx.x, nact);
+  const uint32_t slot0 = (uint32_t)blk * (uint32_t)kEmitChunk;
+  const uint32_t slot1 = (uint32_t)min((uint64_t)slot0 + kEmitChunk, (uint64_t)K);
+  const uint32_t m0 = chunk_first[blk];
+  const uint32_t m_end = slot1 < K ? chunk_first[blk + 1] + 1u : N;
+  const int nr = (int)(m_end - m0);  // records that may own slots of the chunk (<= kEmitChunk + 1)
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  static_assert(kEmitItems == 8, "a thread's slots are one 16-byte word of s_own");
+  uint4* own4 = (uint4*)s_own + threadIdx.x;
+  *own4 = make_uint4(0u, 0u, 0u, 0u);
+  if (threadIdx.x < kRadix) s_hist[threadIdx.x] = 0u;
+  __syncthreads();
+  for (int i = 1 + threadIdx.x; i < nr; i += kEmitThreads) {  // record 0 owns the first slot
+    const uint32_t p = epref[m0 + i];
+    if (p < slot1) s_own[p - slot0] = (uint16_t)i;
   }
   __syncthreads();
-  for (uint32_t slot = slot0 + threadIdx.x; slot < slot1; slot += kScanThreads) {
-    // last staged record whose first position is <= slot
-    int lo = 0, hi = nr;  // invariant: s_pref[lo] <= slot, and slot < s_pref[hi] when hi < nr
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (s_pref[mid] <= slot) lo = mid; else hi = mid;
+  {
+    uint4 q = *own4;
+    uint32_t x[kEmitItems] = {q.x & 0xffffu, q.x >> 16, q.y & 0xffffu, q.y >> 16,
+                              q.z & 0xffffu, q.z >> 16, q.w & 0xffffu, q.w >> 16};
+#pragma unroll
+    for (int j = 1; j < kEmitItems; ++j) x[j] = max(x[j], x[j - 1]);
+    uint32_t incl = x[kEmitItems - 1];
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const uint32_t y = __shfl_up(incl, o, kWave);
+      if (lane >= o) incl = max(incl, y);
     }
-    const uint32_t j = slot - s_pref[lo];
-    const uint32_t wtx = s_wtx[lo], w = wtx & 0xffffu;
-    const uint32_t ty = j / w, tx = j - ty * w;
-    tkey[slot] = s_base[lo] + ty * (wtx >> 16) + tx;
-    tval[slot] = s_off[lo] + j;  // canonical pair index
-    trec[slot] = s_rec[lo];
+    if (lane == kWave - 1) s_wave[wave] = incl;
+    uint32_t before = __shfl_up(incl, 1, kWave);
+    if (lane == 0) before = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kEmitThreads / kWave; ++w) before = w < wave ? max(before, s_wave[w]) : before;
+#pragma unroll
+    for (int j = 0; j < kEmitItems; ++j) x[j] = max(x[j], before);
+    *own4 = make_uint4(x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16), x[6] | (x[7] << 16));
   }
+  __syncthreads();
+  // four slots at a time, their descriptors in flight together
+#pragma unroll
+  for (int j0 = 0; j0 < kEmitItems; j0 += 4) {
+    uint4 d[4];
+    uint32_t p[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t m = m0 + s_own[(j0 + j) * kEmitThreads + threadIdx.x];  // past slot1: the last record
+      d[j] = sdesc[m];
+      p[j] = epref[m];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t slot = slot0 + (j0 + j) * kEmitThreads + threadIdx.x;
+      const uint32_t q = slot - p[j], w = d[j].y & 0xffffu;
+      const uint32_t ty = q / w, tx = q - ty * w;
+      if (slot < slot1) {
+        const uint32_t tile = d[j].x + ty * (d[j].y >> 16) + tx;
+        atomicAdd(&s_hist[tile & (kRadix - 1)], 1u);
+        tkey[slot] = tile;
+        tval[slot] = d[j].z + q;  // canonical pair index
+        trec[slot] = d[j].w;
+      }
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < kRadix) hist[(int64_t)threadIdx.x * nblk + blk] = s_hist[threadIdx.x];
 }
 
 template <typename KT>
@@ -368,19 +466,20 @@ __global__ __launch_bounds__(kSortThreads) void radix_hist(const KT* __restrict_
                                                            uint32_t* __restrict__ hist) {
   __shared__ uint32_t h[kRadix];
   const uint32_t K = effective_count(count, status);
-  h[threadIdx.x] = 0;
+  const int64_t nact = ((int64_t)K + kSortTile - 1) / kSortTile;
+  if ((int64_t)blockIdx.x >= nact) return;  // uniform: a column that is not read
+  if (threadIdx.x < kRadix) h[threadIdx.x] = 0;
   __syncthreads();
-  const int64_t blk = xcd_block((int64_t)blockIdx.x, ((int64_t)K + kSortTile - 1) / kSortTile);
-  const int64_t base = blk * kSortTile;
-  if (base < K) {
-#pragma unroll 4
-    for (int k = 0; k < kSortItems; ++k) {
-      const int64_t i = base + k * kSortThreads + threadIdx.x;
-      if (i < K) atomicAdd(&h[(uint32_t)(keys[i] >> shift) & (kRadix - 1)], 1u);
-    }
-  }
+  const int64_t blk = xcd_block((int64_t)blockIdx.x, nact);
+  const int64_t base = blk * kSortTile + threadIdx.x;
+  KT key[kSortItems];
+#pragma unroll
+  for (int k = 0; k < kSortItems; ++k) key[k] = base + k * kSortThreads < K ? keys[base + k * kSortThreads] : KT(0);
+#pragma unroll
+  for (int k = 0; k < kSortItems; ++k)
+    if (base + k * kSortThreads < K) atomicAdd(&h[(uint32_t)(key[k] >> shift) & (kRadix - 1)], 1u);
   __syncthreads();
-  hist[(int64_t)threadIdx.x * nblk + blk] = h[threadIdx.x];
+  if (threadIdx.x < kRadix) hist[(int64_t)threadIdx.x * nblk + blk] = h[threadIdx.x];
 }
 
 // One block per digit: exclusive scan of that digit's counts over the first
@@ -418,45 +517,69 @@ __global__ __launch_bounds__(256) void radix_digit_scan(uint32_t* __restrict__ h
   if (threadIdx.x == 0) digit_total[blockIdx.x] = s_carry;
 }
 
-// Lanes of the wave holding the same 8-bit digit (among valid lanes).
-__device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid) {
+// Lanes of the wave holding the same digit (among valid lanes), the digit's
+// low `bits` bits alone (the others are zero in every key).
+__device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid, int bits) {
   uint64_t m = __ballot(valid);
+  uint32_t lo = (uint32_t)m, hi = (uint32_t)(m >> 32);
 #pragma unroll
   for (int b = 0; b < 8; ++b) {
-    const bool bit = (d >> b) & 1u;
-    const uint64_t bb = __ballot(bit);
-    m &= bit ? bb : ~bb;
+    if (b >= bits) break;  // uniform
+    const uint32_t t = (uint32_t)(((int32_t)(d << (31 - b))) >> 31);  // the bit, in every position
+    const uint64_t bb = __ballot(t != 0u);
+    lo &= ~((uint32_t)bb ^ t);
+    hi &= ~((uint32_t)(bb >> 32) ^ t);
   }
-  return m;
+  return (uint64_t)lo | ((uint64_t)hi << 32);
+}
+
+// Exclusive scan of one value per thread over the first 256 threads of the
+// block (all threads call it).
+__device__ __forceinline__ uint32_t exclusive_scan_first_256(uint32_t x, uint32_t* s_wave) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  uint32_t incl = x;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const uint32_t y = __shfl_up(incl, o, kWave);
+    if (lane >= o) incl += y;
+  }
+  if (lane == kWave - 1 && wave < kRadix / kWave) s_wave[wave] = incl;
+  __syncthreads();
+  uint32_t off = 0;
+#pragma unroll
+  for (int w = 0; w < kRadix / kWave; ++w) off += w < wave ? s_wave[w] : 0u;
+  __syncthreads();
+  return incl - x + off;
 }
 
 // One stable scatter pass for 32-bit keys; NV value arrays travel with the
 // keys (NV = 1 or 2; the second may be null when NV = 1).  Each wave owns a
-// contiguous quarter (1024 elements) of the block's 4096 and ranks its items
+// contiguous eighth (512 elements) of the block's 4096 and ranks its items
 // in element order against wave-private running digit counts in LDS (match
 // by ballots; only the leader of a digit group updates the count), so the
 // ranking needs no block barrier.  Then one barrier, per-digit prefixes over
-// the four waves, the elements placed in LDS in (digit, index) order, and
-// written out run by run, so consecutive threads write consecutive addresses.
+// the waves, the elements placed in LDS in (digit, index) order, and written
+// out run by run, so consecutive threads write consecutive addresses.  The
+// arrays go through the same 16 KB of LDS in turn: with a buffer for each, two
+// workgroups of 256 threads fitted a CU and a pass over 14.1M pairs with two
+// values took 95 us (3.6 TB/s); now 78 (4.3 TB/s).
 template <int NV>
-__global__ __launch_bounds__(kSortThreads) void radix_scatter(const uint32_t* __restrict__ kin,
+__global__ __launch_bounds__(kSortThreads, 4) void radix_scatter(const uint32_t* __restrict__ kin,
                                                               const uint32_t* __restrict__ vin,
                                                               const uint32_t* __restrict__ vin2,
                                                               uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
                                                               uint32_t* __restrict__ vout2,
                                                               const uint32_t* __restrict__ count,
-                                                              const int32_t* __restrict__ status, int shift,
+                                                              const int32_t* __restrict__ status, int shift, int bits,
                                                               int64_t nblk, const uint32_t* __restrict__ hist,
                                                               const uint32_t* __restrict__ digit_total) {
   constexpr int kWaves = kSortThreads / kWave;
   constexpr int kPerWave = kSortTile / kWaves;
-  __shared__ uint32_t s_gbase[kRadix];  // global position of this block's first element of each digit
+  __shared__ uint32_t s_gbase[kRadix];  // global position of digit d's first element here, less its local position
   __shared__ uint32_t s_lbase[kRadix];  // its position within the block's digit-ordered elements
   __shared__ uint32_t s_cnt[kWaves][kRadix];  // running counts per wave, then the waves' prefixes
   __shared__ uint32_t s_wave[kWaves];
-  __shared__ uint32_t s_k[kSortTile];
-  __shared__ uint32_t s_v[kSortTile];
-  __shared__ uint32_t s_v2[NV == 2 ? kSortTile : 1];
+  __shared__ uint32_t s_buf[kSortTile];
   const uint32_t K = effective_count(count, status);
   const int64_t nact = ((int64_t)K + kSortTile - 1) / kSortTile;
   if ((int64_t)blockIdx.x >= nact) return;  // uniform across the block
@@ -465,28 +588,28 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter(const uint32_t* __
   const int nvalid = (int)min((int64_t)kSortTile, (int64_t)K - base);
   const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) s_cnt[w][t] = 0;
-  __syncthreads();
-  uint32_t key[kSortItems], val[kSortItems], val2[NV == 2 ? kSortItems : 1], rk[kSortItems];
+  for (int q = 0; q < kWaves * kRadix / kSortThreads; ++q) (&s_cnt[0][0])[q * kSortThreads + t] = 0;
+  uint32_t key[kSortItems], val[kSortItems], val2[NV == 2 ? kSortItems : 1], pos[kSortItems];
   const uint64_t lt_mask = (1ull << lane) - 1ull;
   uint32_t* cnt = s_cnt[wave];
+  const int li0 = wave * kPerWave + lane;
 #pragma unroll
-  for (int k = 0; k < kSortItems; ++k) {
-    const int li = wave * kPerWave + k * kWave + lane;
-    const bool valid = li < nvalid;
-    key[k] = valid ? kin[base + li] : 0u;
-    val[k] = valid ? vin[base + li] : 0u;
-    if (NV == 2) val2[k] = valid ? vin2[base + li] : 0u;
+  for (int k = 0; k < kSortItems; ++k) key[k] = li0 + k * kWave < nvalid ? kin[base + li0 + k * kWave] : 0u;
+#pragma unroll
+  for (int k = 0; k < kSortItems; ++k) val[k] = li0 + k * kWave < nvalid ? vin[base + li0 + k * kWave] : 0u;
+  if (NV == 2) {
+#pragma unroll
+    for (int k = 0; k < kSortItems; ++k) val2[k] = li0 + k * kWave < nvalid ? vin2[base + li0 + k * kWave] : 0u;
   }
+  __syncthreads();
 #pragma unroll
   for (int k = 0; k < kSortItems; ++k) {
-    const int li = wave * kPerWave + k * kWave + lane;
-    const bool valid = li < nvalid;
+    const bool valid = li0 + k * kWave < nvalid;
     const uint32_t d = (key[k] >> shift) & (kRadix - 1);
-    const uint64_t peers = match_digit(d, valid);
+    const uint64_t peers = match_digit(d, valid, bits);
     const uint32_t r = __popcll(peers & lt_mask);
     const uint32_t c = valid ? cnt[d] : 0u;  // elements of digit d earlier in this wave
-    rk[k] = c + r;
+    pos[k] = c + r;
     if (valid && r == 0) cnt[d] = c + (uint32_t)__popcll(peers);
     __builtin_amdgcn_wave_barrier();  // the wave's LDS updates stay in item order
   }
@@ -494,39 +617,49 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter(const uint32_t* __
   {
     // digit t: the waves' prefixes and the block's count
     uint32_t run = 0;
+    if (t < kRadix) {
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      const uint32_t c = s_cnt[w][t];
-      s_cnt[w][t] = run;
-      run += c;
+      for (int w = 0; w < kWaves; ++w) {
+        const uint32_t c = s_cnt[w][t];
+        s_cnt[w][t] = run;
+        run += c;
+      }
     }
-    uint32_t tot;
-    const uint32_t lb = block_exclusive_scan_256(run, &tot, s_wave);
-    const uint32_t dbase = block_exclusive_scan_256(digit_total[t], &tot, s_wave);
-    s_lbase[t] = lb;
-    s_gbase[t] = dbase + hist[(int64_t)t * nblk + blk];
+    const uint32_t lb = exclusive_scan_first_256(run, s_wave);
+    const uint32_t dbase = exclusive_scan_first_256(t < kRadix ? digit_total[t] : 0u, s_wave);
+    if (t < kRadix) {
+      s_lbase[t] = lb;
+      s_gbase[t] = dbase + hist[(int64_t)t * nblk + blk] - lb;
+    }
   }
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < kSortItems; ++k) {
-    const int li = wave * kPerWave + k * kWave + lane;
-    if (li < nvalid) {
-      const uint32_t d = (key[k] >> shift) & (kRadix - 1);
-      const uint32_t pos = s_lbase[d] + cnt[d] + rk[k];
-      s_k[pos] = key[k];
-      s_v[pos] = val[k];
-      if (NV == 2) s_v2[pos] = val2[k];
-    }
+    const uint32_t d = (key[k] >> shift) & (kRadix - 1);
+    pos[k] += s_lbase[d] + cnt[d];
+    if (li0 + k * kWave < nvalid) s_buf[pos[k]] = key[k];
   }
   __syncthreads();
-  for (int i = t; i < nvalid; i += kSortThreads) {
-    const uint32_t kk = s_k[i];
-    const uint32_t d = (kk >> shift) & (kRadix - 1);
-    const uint32_t pos = s_gbase[d] + ((uint32_t)i - s_lbase[d]);
-    kout[pos] = kk;
-    vout[pos] = s_v[i];
-    if (NV == 2) vout2[pos] = s_v2[i];
+  uint32_t to[kSortItems];  // global position of the block's digit-ordered element t + k * kSortThreads
+#pragma unroll
+  for (int k = 0; k < kSortItems; ++k) {
+    const int i = k * kSortThreads + t;
+    const uint32_t kk = s_buf[i];
+    to[k] = s_gbase[(kk >> shift) & (kRadix - 1)] + (uint32_t)i;
+    if (i < nvalid) kout[to[k]] = kk;
   }
+  auto move = [&](const uint32_t* v, uint32_t* out) {
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSortItems; ++k)
+      if (li0 + k * kWave < nvalid) s_buf[pos[k]] = v[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSortItems; ++k)
+      if (k * kSortThreads + t < nvalid) out[to[k]] = s_buf[k * kSortThreads + t];
+  };
+  move(val, vout);
+  if (NV == 2) move(val2, vout2);
 }
 
 // Per sorted pair: [start, end) of its tile's run and, if asked for, the
@@ -624,12 +757,8 @@ hipError_t launch_fill_u32(uint32_t* p, int64_t count, uint32_t value, hipStream
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct SortWs {
-  uint32_t* block_sums;     // [scan blocks] pairs per block of records
-  uint32_t* vis_sums;       // [scan blocks] visible records per block
-  uint32_t* block_offsets;  // canonical emission offset of each block
-  uint32_t* vis_offsets;    // compaction offset of each block
-  uint32_t* eblock_sums;    // pairs per block of depth-sorted records
-  uint32_t* eblock_offsets;
+  uint2* block_sums;        // [record blocks] pairs and visible records per block, then their scans
+  uint2* eblock_sums;       // [emission scan blocks] pairs per block of depth-sorted records, then their scan
   uint32_t* nvis;           // [1] number of visible records
   uint32_t* dkey;           // [nrec] depth bits of the visible records
   uint32_t* dval;           // [nrec] their compact indices
@@ -659,12 +788,8 @@ static SortWs carve(const SortPlan& p, uint64_t capacity, void* ws) {
     return q;
   };
   const size_t nb = (size_t)p.scan_blocks, nrec = (size_t)p.nrec;
-  w.block_sums = take(4 * nb);
-  w.vis_sums = take(4 * nb);
-  w.block_offsets = take(4 * nb);
-  w.vis_offsets = take(4 * nb);
-  w.eblock_sums = take(4 * nb);
-  w.eblock_offsets = take(4 * nb);
+  w.block_sums = (uint2*)take(8 * (size_t)p.rec_blocks);
+  w.eblock_sums = (uint2*)take(8 * nb);
   w.nvis = take(8);  // [0] visible records, [1] their pairs (unused)
   w.dkey = take(4 * nrec);
   w.dval = take(4 * nrec);
@@ -689,20 +814,23 @@ size_t bin_sort_ws_bytes(const SortPlan& p) { return carve(p, p.capacity, nullpt
 
 // One stable LSD pass per 8 key bits; the result lands back in (k0, v0, u0)
 // when the number of passes is even and in (k1, v1, u1) when it is odd.
+// counted: the first pass's histogram is there.
 template <typename KT, int NV>
-static void radix_sort(KT* k0, uint32_t* v0, uint32_t* u0, KT* k1, uint32_t* v1, uint32_t* u1, int passes,
-                       const uint32_t* count, const int32_t* status, int64_t nblk, const SortWs& w, hipStream_t s) {
+static void radix_sort(KT* k0, uint32_t* v0, uint32_t* u0, KT* k1, uint32_t* v1, uint32_t* u1, int key_bits,
+                       const uint32_t* count, const int32_t* status, int64_t nblk, bool counted, const SortWs& w,
+                       hipStream_t s) {
   KT* kb[2] = {k0, k1};
   uint32_t* vb[2] = {v0, v1};
   uint32_t* ub[2] = {u0, u1};
   int cur = 0;
-  for (int p = 0; p < passes && nblk > 0; ++p) {
-    const int shift = 8 * p;
-    hipLaunchKernelGGL((radix_hist<KT>), dim3((unsigned)nblk), dim3(kSortThreads), 0, s, kb[cur], count, status,
-                       shift, nblk, w.hist);
+  for (int shift = 0; shift < key_bits && nblk > 0; shift += 8) {
+    const int bits = key_bits - shift < 8 ? key_bits - shift : 8;
+    if (shift > 0 || !counted)
+      hipLaunchKernelGGL((radix_hist<KT>), dim3((unsigned)nblk), dim3(kSortThreads), 0, s, kb[cur], count, status,
+                         shift, nblk, w.hist);
     hipLaunchKernelGGL(radix_digit_scan, dim3(kRadix), dim3(256), 0, s, w.hist, nblk, count, status, w.digit_total);
     hipLaunchKernelGGL((radix_scatter<NV>), dim3((unsigned)nblk), dim3(kSortThreads), 0, s, kb[cur], vb[cur],
-                       ub[cur], kb[cur ^ 1], vb[cur ^ 1], ub[cur ^ 1], count, status, shift, nblk, w.hist,
+                       ub[cur], kb[cur ^ 1], vb[cur ^ 1], ub[cur ^ 1], count, status, shift, bits, nblk, w.hist,
                        w.digit_total);
     cur ^= 1;
   }
@@ -717,41 +845,41 @@ hipError_t launch_bin_sort(const SortPlan& plan, const float4* splats, const uin
   const int64_t nb = plan.scan_blocks;
   uint32_t* count = out.count;
   int32_t* status = out.status;
-  if (nb > 0)
-    hipLaunchKernelGGL(count_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, s, tiles_touched, plan.nrec,
-                       w.block_sums, w.vis_sums);
-  // K and the capacity status, then the number of visible records
-  hipLaunchKernelGGL(scan_top, dim3(1), dim3(1024), 0, s, w.block_sums, nb, w.block_offsets, capacity, count, status);
-  hipLaunchKernelGGL(scan_top, dim3(1), dim3(1024), 0, s, w.vis_sums, nb, w.vis_offsets, (uint64_t)0, w.nvis,
-                     (int32_t*)nullptr);
+  const int64_t rb = plan.rec_blocks;
+  if (rb > 0)
+    hipLaunchKernelGGL(count_reduce, dim3((unsigned)rb), dim3(kScanThreads), 0, s, tiles_touched, plan.nrec,
+                       w.block_sums);
+  // K and the capacity status, and the number of visible records
+  hipLaunchKernelGGL(scan_top, dim3(1), dim3(1024), 0, s, w.block_sums, rb, (const uint32_t*)nullptr,
+                     capacity, count, w.nvis, status);
   if (nb > 0) {
-    hipLaunchKernelGGL(compact_visible, dim3((unsigned)nb), dim3(kScanThreads), 0, s, splats, tiles_touched,
-                       plan.nrec, n, vt, inv_tw, inv_th, w.block_offsets, w.vis_offsets, status, out.offsets, w.dkey,
-                       w.dval, w.desc, out.keys ? w.drec : (uint32_t*)nullptr);
+    hipLaunchKernelGGL(compact_visible, dim3((unsigned)rb), dim3(kScanThreads), 0, s, splats, tiles_touched,
+                       plan.nrec, n, vt, inv_tw, inv_th, w.block_sums, status, out.offsets, w.dkey, w.dval, w.desc,
+                       out.keys ? w.drec : (uint32_t*)nullptr);
     // depth order of the visible records (four passes: the result is back in dkey/dval)
-    radix_sort<uint32_t, 1>(w.dkey, w.dval, nullptr, w.dkey_alt, w.dval_alt, nullptr, 4, w.nvis, status,
-                            plan.rec_sort_blocks, w, s);
-    hipLaunchKernelGGL(gather_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, s, w.desc, w.dval, w.nvis, status,
-                       w.sdesc, w.eblock_sums);
-    hipLaunchKernelGGL(scan_top, dim3(1), dim3(1024), 0, s, w.eblock_sums, nb, w.eblock_offsets, (uint64_t)0,
-                       w.nvis + 1, (int32_t*)nullptr);  // total unused (equals K)
-    // per-record emission offsets (in dkey_alt, free after the depth sort), then
-    // emit so that the tile sort ends in (tkey, pair_index, ids)
+    radix_sort<uint32_t, 1>(w.dkey, w.dval, nullptr, w.dkey_alt, w.dval_alt, nullptr, 32, w.nvis, status,
+                            plan.rec_sort_blocks, false, w, s);
+    // the emission's positions go to dkey_alt, free after the depth sort
     uint32_t* epref = w.dkey_alt;
-    hipLaunchKernelGGL(emit_prefix, dim3((unsigned)nb), dim3(kScanThreads), 0, s, w.sdesc, w.nvis, w.eblock_offsets,
-                       status, epref, w.chunk_first);
-    const bool even = plan.tile_passes % 2 == 0;
+    hipLaunchKernelGGL(gather_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, s, w.desc, w.dval, w.nvis, status,
+                       vt, w.sdesc, epref, w.eblock_sums);
+    hipLaunchKernelGGL(scan_top, dim3(1), dim3(1024), 0, s, w.eblock_sums, nb, w.nvis, (uint64_t)0,
+                       w.nvis + 1, (uint32_t*)nullptr, (int32_t*)nullptr);  // total unused (equals K)
+    // emit so that the tile sort ends in (tkey, pair_index, ids)
+    hipLaunchKernelGGL(emit_prefix, dim3((unsigned)nb), dim3(kScanThreads), 0, s, w.nvis, count, w.eblock_sums, status,
+                       epref, w.chunk_first);
+    const bool even = (plan.tile_bits + 7) / 8 % 2 == 0;
     const int64_t emit_blocks = ((int64_t)capacity + kEmitChunk - 1) / kEmitChunk;
     if (emit_blocks > 0)
-      hipLaunchKernelGGL(emit_pairs, dim3((unsigned)emit_blocks), dim3(kScanThreads), 0, s, w.sdesc, epref,
-                         w.chunk_first, w.nvis, count, status, vt, even ? w.tkey : w.tkey_alt,
-                         even ? out.pair_index : w.tval_alt, even ? out.ids : w.trec_alt);
+      hipLaunchKernelGGL(emit_pairs, dim3((unsigned)emit_blocks), dim3(kEmitThreads), 0, s, w.sdesc, epref,
+                         w.chunk_first, w.nvis, count, status, even ? w.tkey : w.tkey_alt,
+                         even ? out.pair_index : w.tval_alt, even ? out.ids : w.trec_alt, plan.sort_blocks, w.hist);
     if (even)
-      radix_sort<uint32_t, 2>(w.tkey, out.pair_index, out.ids, w.tkey_alt, w.tval_alt, w.trec_alt, plan.tile_passes,
-                              count, status, plan.sort_blocks, w, s);
+      radix_sort<uint32_t, 2>(w.tkey, out.pair_index, out.ids, w.tkey_alt, w.tval_alt, w.trec_alt, plan.tile_bits,
+                              count, status, plan.sort_blocks, true, w, s);
     else
-      radix_sort<uint32_t, 2>(w.tkey_alt, w.tval_alt, w.trec_alt, w.tkey, out.pair_index, out.ids, plan.tile_passes,
-                              count, status, plan.sort_blocks, w, s);
+      radix_sort<uint32_t, 2>(w.tkey_alt, w.tval_alt, w.trec_alt, w.tkey, out.pair_index, out.ids, plan.tile_bits,
+                              count, status, plan.sort_blocks, true, w, s);
   }
   const int64_t cap_blocks = ((int64_t)capacity + 1023) / 1024;
   if (cap_blocks > 0 && nb > 0)

@@ -160,10 +160,11 @@ SortPlan sort_plan(int64_t n, int32_t V, int32_t total_tiles, uint64_t capacity)
   SortPlan p;
   p.nrec = (int64_t)V * n;
   p.capacity = capacity;
+  p.rec_blocks = (p.nrec + 4095) / 4096;
   p.scan_blocks = (p.nrec + 1023) / 1024;
   p.rec_sort_blocks = (p.nrec + 4095) / 4096;
   p.sort_blocks = (int64_t)((capacity + 4095) / 4096);
-  p.tile_passes = ((total_tiles > 1 ? ilog2(total_tiles) : 0) + 7) / 8;
+  p.tile_bits = total_tiles > 1 ? ilog2(total_tiles) : 0;
   return p;
 }
 

@@ -115,6 +115,18 @@ __device__ __forceinline__ float wave_sum_lane63(float v) {
   return v;
 }
 
+// Inclusive prefix sums over the 64 lanes (row shifts by 1, 2, 4, 8, then the
+// rows' totals by broadcasts).
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);
+  return v;
+}
+
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
 // The wave's earlier LDS writes are visible to all its lanes' later LDS

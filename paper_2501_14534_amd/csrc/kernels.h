@@ -203,10 +203,11 @@ hipError_t launch_significance(const float* log_scales, const float* opacity_log
 struct SortPlan {
   int64_t nrec;             // V * n
   uint64_t capacity;        // pair capacity
-  int64_t scan_blocks;      // records / 1024
+  int64_t rec_blocks;       // records / 4096 (count and compaction)
+  int64_t scan_blocks;      // records / 1024 (emission of the visible records)
   int64_t rec_sort_blocks;  // records / 4096 (depth sort of the visible records)
   int64_t sort_blocks;      // capacity / 4096 (tile sort of the pairs)
-  int tile_passes;          // 8-bit passes over ceil(log2 #tiles) tile bits
+  int tile_bits;            // ceil(log2 #tiles), sorted in passes of 8
 };
 
 hipError_t launch_project(const ProjectArgs& a, const ViewTable& vt, int deg, hipStream_t s);

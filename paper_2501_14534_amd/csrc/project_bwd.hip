@@ -93,18 +93,6 @@ __device__ __forceinline__ float acc_mul_add(float t, float a, float b) {
   return t + p;
 }
 
-// Inclusive prefix sums over the 64 lanes (row shifts by 1, 2, 4, 8, then the
-// rows' totals by broadcasts).
-__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);
-  return v;
-}
-
 // Sums of the 9 pair gradients of each lane's record (cnt pairs from pair
 // index off; cnt = 0 gives zeros), accumulated in double and rounded once to
 // float.  Called by all 64 lanes of a wave together, for records of
