@@ -247,6 +247,7 @@ RenderArgs render_args(const gs_projected* p, const gs_binning* b, const gs_opts
   a.batch = o->batch_depth;
   a.ppt = o->pixels_per_thread;
   a.cull = o->subtile_cull;
+  a.zero_rows = 0;
   for (int c = 0; c < 3; ++c) a.bg[c] = o->bg[c];
   a.log2_chunk = log2_chunk(o);
   a.nslots = chunk_slots(b->capacity, o);
@@ -559,6 +560,7 @@ int gs_blend_bwd(const gs_camera* cams, int32_t V, int64_t n, const gs_opts* opt
   if (d != GS_OK) return d;
   RenderArgs ra = render_args(proj, bins, opts);
   attach_state(&ra, bins->capacity, (int64_t)V * n, opts, ws);
+  ra.zero_rows = 1;  // the caller's grad_pair: the rows of all walked pairs
   const hipError_t e =
       launch_fill_u32((uint32_t*)ra.pair_live, (int64_t)(live_bytes(bins->capacity) / 4), 0u, (hipStream_t)stream);
   if (e != hipSuccess) return GS_E_HIP;

@@ -41,6 +41,7 @@ struct RenderArgs {
   int32_t batch;
   int32_t ppt;
   int32_t cull;
+  int32_t zero_rows;  // backward: also write the rows (zeros) of the walked pairs that no pixel composites
   float bg[3];
   // per-chunk pixel states written by the forward, read by the backward:
   // boundary position q = start + k * 2^log2_chunk (k >= 1) of a tile's list

@@ -194,17 +194,23 @@ __device__ __forceinline__ uint64_t chunk_bits(const uint16_t* s_mask, int c, in
 }
 
 // Dynamic LDS of the blend kernels, sized by the batch depth B and the wave count W:
-//   records 3 x B float4 | [bwd] B pair indices | [bwd] W x B x 9 partial sums | B masks
+//   records 3 x B float4 | [bwd] W x B x 9 partial sums | [bwd] B pair indices | B masks | [bwd] B rows
 struct Lds {
   float4 *a, *b, *c;
   uint32_t* e;
   float* part;
   uint16_t* mask;
+  uint16_t* row;
 };
+
+// Partial sums, in whole float4.
+__host__ __device__ inline size_t part_bytes(int batch, int nwaves) {
+  return (4 * (size_t)GS_GRAD_FLOATS * nwaves * batch + 15) & ~(size_t)15;
+}
 
 __host__ __device__ inline size_t lds_bytes(int batch, int nwaves, bool bwd) {
   size_t o = 3 * 16 * (size_t)batch;
-  if (bwd) o += 4 * (size_t)batch + 4 * (size_t)GS_GRAD_FLOATS * nwaves * batch;
+  if (bwd) o += part_bytes(batch, nwaves) + 4 * (size_t)batch + 2 * (size_t)batch;
   o += 2 * (size_t)batch;
   return (o + 15) & ~(size_t)15;
 }
@@ -218,10 +224,11 @@ __device__ inline Lds lds_carve(unsigned char* base, int batch, int nwaves, bool
   l.e = nullptr;
   l.part = nullptr;
   if (bwd) {
+    l.part = (float*)(base + o), o += part_bytes(batch, nwaves);
     l.e = (uint32_t*)(base + o), o += 4 * (size_t)batch;
-    l.part = (float*)(base + o), o += 4 * (size_t)GS_GRAD_FLOATS * nwaves * batch;
   }
-  l.mask = (uint16_t*)(base + o);
+  l.mask = (uint16_t*)(base + o), o += 2 * (size_t)batch;
+  l.row = (uint16_t*)(base + o);
   return l;
 }
 
@@ -869,8 +876,10 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
                                          const int32_t* __restrict__ last_in, const LossIn& loss,
                                          float* __restrict__ grad_pair, int64_t item, unsigned char* smem,
                                          bool ok = true, int walked = -1) {
+  constexpr int kMaxChunks = 8;  // of 64 entries in a batch
   __shared__ int s_max[4];
   __shared__ Box s_box[4 * PPT];  // live box of every wave's blocks
+  __shared__ uint64_t s_hit[kMaxChunks][4];  // entries of a chunk that a wave added to
   const int lg = a.log2_chunk;
   int gtile;
   bool first;
@@ -960,11 +969,15 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
   maxlast = min(maxlast, (int)(tc.end - tc.start));  // never walk past the tile's list
   const uint64_t wlim = (uint64_t)tc.start + (uint64_t)maxlast;
 
-  // Pairs behind every pixel's last contributor receive no gradient: their rows
-  // are not written and their live bytes stay 0 (cleared before the launch), so
-  // the per-record sums skip them.  (About 4 in 5 pairs at 1M Gaussians:
-  // writing zero rows at their scattered emission positions cost more than the
-  // rest of the walk's stores.)
+  // Pairs that no pixel composites receive no gradient: their rows are not
+  // written and their live bytes stay 0 (cleared before the launch), so the
+  // per-record sums skip them.  (About 4 in 5 pairs at 1M Gaussians lie behind
+  // every pixel's last contributor: writing zero rows at their scattered
+  // emission positions cost more than the rest of the walk's stores; half of the
+  // others are culled or miss every pixel: leaving those out too took the walk
+  // from 427 to 406 us and the sums from 95 to 81 at 1M Gaussians in eight
+  // views, from 2590 to 2530 and from 490 to 421 at 6M.)  With a.zero_rows the
+  // pairs in front of the last contributor get their rows all the same.
 
   // Starting state at the chunk's end: the final one when the walk ends in
   // this chunk, else the forward's record at ce (transmittance there, and the
@@ -1024,13 +1037,19 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
       s_c[i] = a.splats[(size_t)rec * 3 + 2];
       if (CULL) s_mask[i] = (uint16_t)footprint_mask(ra, rb, nwaves * PPT, s_box);
     }
-    for (int i = threadIdx.x; i < nwaves * batch * GS_GRAD_FLOATS; i += nthreads) s_part[i] = 0.0f;
-    __syncthreads();
     const int nchunks = (cnt + kWave - 1) / kWave;
+#pragma unroll 1
+    for (int i = threadIdx.x; i < (int)(part_bytes(batch, nwaves) / 16); i += nthreads)
+      ((float4*)s_part)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    __syncthreads();
     for (int c = nchunks - 1; c >= 0; --c) {
       uint64_t mp[PPT];
       uint64_t m = chunk_bits<PPT, CULL>(s_mask, c, cnt, wave, lane, mp);
-      if (m == 0) continue;
+      if (m == 0) {
+        if (lane == 0) s_hit[c][wave] = 0;
+        continue;
+      }
+      uint64_t hit = 0;
       // one staged record: per-pixel partials, then the wave's sums into LDS
       auto grad = [&](int j, const float4& ra, const float4& rb, const float4& rc) {
         const int jr = (int)(bs - tc.start) + j;                   // index within the tile's list
@@ -1071,6 +1090,7 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
           }
         }
         if (any != 0) {  // wave-uniform: the whole wave takes part
+          hit |= 1ull << (j - c * kWave);
           const float v = reduce_scatter9(x, b2, b3);
           if (writer) s_part[(wave * batch + j) * GS_GRAD_FLOATS + my_e] = v * escale;
         }
@@ -1095,11 +1115,25 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
         grad(j1, a1, b1, c1);
         if (!more2) break;
       }
+      if (lane == 0) s_hit[c][wave] = hit;
+    }
+    __syncthreads();
+    // the entries with rows, in order
+    int rows = 0;
+#pragma unroll 1
+    for (int c = 0; c < nchunks; ++c) {
+      uint64_t h = 0;
+#pragma unroll 1
+      for (int w = 0; w < nwaves; ++w) h |= s_hit[c][w];
+      if (a.zero_rows) h = cnt - c * kWave < kWave ? (1ull << (cnt - c * kWave)) - 1ull : ~0ull;
+      if (wave == c % nwaves && ((h >> lane) & 1ull))
+        L.row[rows + __popcll(h & ((1ull << lane) - 1ull))] = (uint16_t)(c * kWave + lane);
+      rows += __popcll(h);
     }
     __syncthreads();
     // fixed-order sum over the waves, one store per (pair, attribute)
-    for (int i = threadIdx.x; i < cnt * GS_GRAD_FLOATS; i += nthreads) {
-      const int j = i / GS_GRAD_FLOATS, k = i - j * GS_GRAD_FLOATS;
+    for (int i = threadIdx.x; i < rows * GS_GRAD_FLOATS; i += nthreads) {
+      const int r = i / GS_GRAD_FLOATS, k = i - r * GS_GRAD_FLOATS, j = L.row[r];
       auto total = [&](int e) {
         float t = s_part[j * GS_GRAD_FLOATS + e];
         for (int w = 1; w < nwaves; ++w) t += s_part[(w * batch + j) * GS_GRAD_FLOATS + e];
@@ -1118,8 +1152,13 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
   }
 }
 
+// Held to 64, 80 and 96 registers at 1, 2 and 4 pixels a thread: 8, 6 and 5
+// waves per SIMD (at 4 it took 103, 4 waves, without).
+template <int PPT>
+constexpr int bwd_waves() { return PPT == 1 ? 8 : PPT == 2 ? 6 : 5; }
 template <int PPT, bool CULL>
-__global__ __launch_bounds__(256) void render_bwd_kernel(RenderArgs a, ViewTable vt, const float* __restrict__ T_final,
+__global__ __launch_bounds__(256, bwd_waves<PPT>()) void render_bwd_kernel(RenderArgs a, ViewTable vt,
+                                                         const float* __restrict__ T_final,
                                                          const int32_t* __restrict__ last_in,
                                                          const float* __restrict__ dL_dimage,
                                                          float* __restrict__ grad_pair) {
