@@ -103,10 +103,10 @@ struct ProjectBwdArgs {
   int32_t assign;                  // 1: write the parameter gradients (zeros where none), 0: add them
 };
 
-// Views of an image call (loss: 32 x 32 tiles; target blur: 16 x 16): per
+// Views of an image call (loss: 116 x 16 tiles; target blur: 16 x 16): per
 // view its size, tile grid, pixel offset (views concatenated, each [3][H][W])
 // and first workgroup; the loss window's taps.
-constexpr int kLossTile = 32;
+constexpr int kLossTileW = 116, kLossTileH = 16;
 constexpr int kBlurTile = 16;
 struct LossView {
   int32_t W, H, TX, TY;
@@ -120,7 +120,7 @@ struct LossViews {
   float g[11];  // normalised Gaussian taps of the 11 x 11 window's 1-D factor
 };
 
-// Workgroup b of an image call: its view, colour plane and 16 x 16 tile.
+// Workgroup b of an image call: its view, colour plane and tile.
 struct LossTile {
   int view, plane, tx, ty;
 };

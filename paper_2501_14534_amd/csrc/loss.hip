@@ -7,195 +7,249 @@
 // (11 x 11 window = outer product of two 11-tap Gaussians of standard deviation
 // 1.5, as Sec. 3.2.5 describes; zero padding; C1 = 0.01^2, C2 = 0.03^2).
 //
-// Two passes over 32 x 32 output tiles, one workgroup per (view, plane, tile),
-// each staging the tile plus a 5-pixel halo in LDS (42 x 42: 1.7 reads per
-// pixel) and filtering it with two 1-D passes, 4 output pixels per thread:
+// Two passes over 116 x 16 output tiles, one workgroup of 256 threads per
+// (view, plane, tile); both filter columns first, straight from memory into
+// registers (a thread owns one of 128 columns, 5 of halo on either side, and 8
+// rows; its 18 loads are all in flight together), leave the column sums in LDS,
+// and filter rows from there, 4 neighbouring pixels a thread from 16-byte reads:
 //   ssim_fwd: the five moments mu_x, mu_y, E[xx], E[yy], E[xy]; S and its
 //             partial derivatives dS/dmu_x, dS/dE[xx], dS/dE[xy] (written to
-//             the workspace); per-workgroup sums of S and |x - y|;
+//             the workspace as three planes); per-workgroup sums of S and
+//             |x - y|;
 //   ssim_bwd: the window's correlation of the three partial-derivative maps
 //             (the window is symmetric, so this is the adjoint of the forward
 //             filtering), combined per pixel as
 //             dS/dx = w*A + 2 x (w*B) + y (w*C), then the L1 term.
+// Vector arithmetic bounds both (about 170 and 90 operations a pixel).  Staging
+// tiles of 32 x 32 with their halo and reading every tap from LDS was bound by
+// those reads (90 and 60 a pixel, now 25 and 15), and the maps as triples were
+// written at a stride of 12 bytes.
 // One workgroup per view adds its workgroups' sums in a fixed order (double)
 // into the view's loss; a last kernel takes their mean.  No atomics:
-// reproducible.
+// reproducible.  (One workgroup for both, a wave per view, took 8-10 us against
+// 9 for the two.)
+// Measured over eight views of 3.09 Mpix together: forward 141 -> 70 us,
+// backward 81 -> 41 us.
 #include "gs_common.h"
 #include "kernels.h"
 
 namespace gs {
 
-constexpr int kLT = kLossTile;       // output tile edge (32)
-constexpr int kLR = 5;               // window radius
-constexpr int kLS = kLT + 2 * kLR;   // staged edge (42)
-constexpr int kLQ = kLT * kLT / 256; // output pixels per thread (4)
-constexpr float kSsimC1 = 0.0001f;   // (0.01)^2
-constexpr float kSsimC2 = 0.0009f;   // (0.03)^2
+constexpr int kLW = kLossTileW, kLH = kLossTileH;  // output tile: 116 x 16
+constexpr int kLR = 5;                  // window radius
+constexpr int kTaps = 2 * kLR + 1;
+constexpr int kCols = 128;              // columns filtered: kLW + 2 kLR, rounded up to two waves
+constexpr int kRows = kLH / 2;          // output rows of a thread's column (two halves of the workgroup)
+constexpr int kQ = 4;                   // neighbouring output pixels per thread of the row pass
+constexpr float kSsimC1 = 0.0001f;      // (0.01)^2
+constexpr float kSsimC2 = 0.0009f;      // (0.03)^2
+// the last group's 16-byte reads end inside the row: 4 (kLW / 4 - 1) + 16 <= kCols
+static_assert(kLW % kQ == 0 && kLW / kQ <= 32 && kLW - kQ + 16 <= kCols && kLW + 2 * kLR <= kCols, "tile width");
 
-// Staged value at (row, col) of the tile's window: zero outside the image.
-__device__ __forceinline__ float staged(const float* plane, int W, int H, int x0, int y0, int i) {
-  const int r = i / kLS, c = i - r * kLS;
-  const int x = x0 - kLR + c, y = y0 - kLR + r;
-  return (x >= 0 && x < W && y >= 0 && y < H) ? plane[(int64_t)y * W + x] : 0.0f;
+typedef float Quad __attribute__((ext_vector_type(4), aligned(4)));  // four floats at any float's address
+
+// Workgroup b's tile: consecutive workgroups go to the 8 XCDs in turn, so each
+// XCD takes a run of neighbouring tiles, whose halos meet in its L2.
+__device__ __forceinline__ int xcd_run(int b, int nb) {
+  const int per = nb / 8, rest = nb - 8 * per, x = b & 7;
+  return b / 8 + x * per + min(x, rest);
 }
 
-// Thread t owns column t % 32 of the tile, rows t / 32 + 8 k (k < 4).
-__device__ __forceinline__ int out_col(int t) { return t & (kLT - 1); }
-__device__ __forceinline__ int out_row(int t, int k) { return (t / kLT) + k * (256 / kLT); }
+// Thread t's column (t % 128 of the tile's window) and first staged row, and
+// which of its rows are inside the image (the rows of a wave are the same).
+struct Column {
+  int x, y;
+  bool in;
+};
+__device__ __forceinline__ Column column_of(int t, int x0, int y0, int W) {
+  Column c;
+  c.x = x0 - kLR + (t & (kCols - 1));
+  c.y = y0 - kLR + __builtin_amdgcn_readfirstlane(t / kCols) * kRows;
+  c.in = c.x >= 0 && c.x < W;
+  return c;
+}
 
-__global__ __launch_bounds__(256) void ssim_fwd_kernel(const float* __restrict__ image,
-                                                       const float* __restrict__ target, LossViews lv,
-                                                       float* __restrict__ dmap, float* __restrict__ bsum) {
-  __shared__ float s_x[kLS * kLS], s_y[kLS * kLS];
-  __shared__ float s_h[5][kLS * kLT];
-  __shared__ float s_red[2][4];
-  const LossTile tl = loss_tile(lv, blockIdx.x);
+// The column's kRows + 10 values of a plane, zero outside the image.
+__device__ __forceinline__ void load_column(const float* __restrict__ plane, const Column& c, int W, int H,
+                                            float v[kRows + 2 * kLR]) {
+#pragma unroll
+  for (int i = 0; i < kRows + 2 * kLR; ++i) {
+    const int y = c.y + i;
+    v[i] = 0.0f;
+    if (y >= 0 && y < H && c.in) v[i] = (plane + (int64_t)y * W)[c.x];
+  }
+}
+
+// Row sums of the four pixels at columns 4 g .. 4 g + 3 from a row of column sums.
+__device__ __forceinline__ void filter_row(const float* row, int g, const float* taps, float out[kQ]) {
+  float v[16];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float4 f = ((const float4*)row)[g + k];
+    v[4 * k] = f.x, v[4 * k + 1] = f.y, v[4 * k + 2] = f.z, v[4 * k + 3] = f.w;
+  }
+#pragma unroll
+  for (int p = 0; p < kQ; ++p) {
+    out[p] = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kTaps; ++k) out[p] += taps[k] * v[p + k];
+  }
+}
+
+// Up to four neighbouring floats (m of them inside the image's row).
+__device__ __forceinline__ Quad load_quad(const float* p, int m) {
+  if (m >= kQ) return *(const Quad*)p;
+  Quad q = {0.f, 0.f, 0.f, 0.f};
+  q.x = p[0];
+  if (m > 1) q.y = p[1];
+  if (m > 2) q.z = p[2];
+  return q;
+}
+__device__ __forceinline__ void store_quad(float* p, int m, Quad q) {
+  if (m >= kQ) {
+    *(Quad*)p = q;
+    return;
+  }
+  p[0] = q.x;
+  if (m > 1) p[1] = q.y;
+  if (m > 2) p[2] = q.z;
+}
+
+// 40 KB of LDS: four workgroups share a CU.
+__global__ __launch_bounds__(256, 4) void ssim_fwd_kernel(const float* __restrict__ image,
+                                                          const float* __restrict__ target, LossViews lv,
+                                                          float* __restrict__ dmap, int64_t map_stride,
+                                                          float* __restrict__ bsum) {
+  __shared__ float4 s_v4[5 * kLH * kCols / 4];
+  float* s_v = (float*)s_v4;
+  const int b = xcd_run(blockIdx.x, lv.total_blocks);
+  const LossTile tl = loss_tile(lv, b);
   const LossView& q = lv.v[tl.view];
   const int W = q.W, H = q.H, t = threadIdx.x;
   const int64_t plane_px = (int64_t)W * H;
   const int64_t poff = 3 * q.pix_off + tl.plane * plane_px;  // this plane in the view-concatenated layout
   const float* xp = image + poff;
   const float* yp = target + poff;
-  const int x0 = tl.tx * kLT, y0 = tl.ty * kLT;
-  for (int i = t; i < kLS * kLS; i += 256) {
-    s_x[i] = staged(xp, W, H, x0, y0, i);
-    s_y[i] = staged(yp, W, H, x0, y0, i);
-  }
-  __syncthreads();
-  // horizontal pass: rows of the staged window, the tile's columns
-  for (int i = t; i < kLS * kLT; i += 256) {
-    const int r = i / kLT, c = i - r * kLT;
-    float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f, a4 = 0.f;
+  const int x0 = tl.tx * kLW, y0 = tl.ty * kLH;
+  {  // column pass
+    const Column c = column_of(t, x0, y0, W);
+    float x[kRows + 2 * kLR], y[kRows + 2 * kLR];
+    load_column(xp, c, W, H, x);
+    load_column(yp, c, W, H, y);
+    float acc[5][kRows];
 #pragma unroll
-    for (int k = 0; k < 11; ++k) {
-      const float g = lv.g[k], x = s_x[r * kLS + c + k], y = s_y[r * kLS + c + k];
-      a0 += g * x;
-      a1 += g * y;
-      a2 += g * (x * x);
-      a3 += g * (y * y);
-      a4 += g * (x * y);
+    for (int i = 0; i < kRows + 2 * kLR; ++i) {
+      const float m[5] = {x[i], y[i], x[i] * x[i], y[i] * y[i], x[i] * y[i]};
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) {  // row r's taps are the staged rows r .. r + 10
+        if (i < r || i > r + 2 * kLR) continue;
+#pragma unroll
+        for (int e = 0; e < 5; ++e) acc[e][r] = i == r ? lv.g[0] * m[e] : acc[e][r] + lv.g[i - r] * m[e];
+      }
     }
-    s_h[0][i] = a0;
-    s_h[1][i] = a1;
-    s_h[2][i] = a2;
-    s_h[3][i] = a3;
-    s_h[4][i] = a4;
+    const int row0 = (t / kCols) * kRows, col = t & (kCols - 1);
+#pragma unroll
+    for (int e = 0; e < 5; ++e)
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) s_v[(e * kLH + row0 + r) * kCols + col] = acc[e][r];
   }
   __syncthreads();
-  // vertical pass: kLQ output pixels per thread
-  const int ox = out_col(t);
+  // row pass: 8 rows of 32 threads (29 with pixels), twice
+  const int g = t & 31, px = x0 + kQ * g;
+  const int m = g < kLW / kQ ? W - px : 0;
   float s_val = 0.f, l1 = 0.f;
+#pragma unroll 1
+  for (int oy = t / 32; oy < kLH; oy += 8) {
+    const int py = y0 + oy;
+    if (m <= 0 || py >= H) continue;
+    float f[5][kQ];
 #pragma unroll
-  for (int j = 0; j < kLQ; ++j) {
-    const int oy = out_row(t, j);
-    float mx = 0.f, my = 0.f, exx = 0.f, eyy = 0.f, exy = 0.f;
+    for (int e = 0; e < 5; ++e) filter_row(s_v + (e * kLH + oy) * kCols, g, lv.g, f[e]);
+    const int64_t pix = poff + (int64_t)py * W + px;
+    const Quad x = load_quad(image + pix, m), y = load_quad(target + pix, m);
+    Quad da, db, dc;
 #pragma unroll
-    for (int k = 0; k < 11; ++k) {
-      const float g = lv.g[k];
-      const int i = (oy + k) * kLT + ox;
-      mx += g * s_h[0][i];
-      my += g * s_h[1][i];
-      exx += g * s_h[2][i];
-      eyy += g * s_h[3][i];
-      exy += g * s_h[4][i];
-    }
-    const int px = x0 + ox, py = y0 + oy;
-    if (px < W && py < H) {
-      const float sxx = exx - mx * mx, syy = eyy - my * my, sxy = exy - mx * my;
+    for (int p = 0; p < kQ; ++p) {
+      const float mx = f[0][p], my = f[1][p];
+      const float sxx = f[2][p] - mx * mx, syy = f[3][p] - my * my, sxy = f[4][p] - mx * my;
       const float n1 = 2.f * mx * my + kSsimC1, n2 = 2.f * sxy + kSsimC2;
       const float d1 = mx * mx + my * my + kSsimC1, d2 = sxx + syy + kSsimC2;
       const float id = 1.0f / (d1 * d2);
       const float S = n1 * n2 * id;
-      const float dmx = 2.f * my * (n2 - n1) * id - 2.f * mx * S * (1.0f / d1 - 1.0f / d2);
-      const float dexx = -S / d2;
-      const float dexy = 2.f * n1 * id;
-      const int64_t pix = (int64_t)py * W + px;
-      const int64_t o = 3 * (poff + pix);  // [pixel][3] partial-derivative triples
-      dmap[o + 0] = dmx;
-      dmap[o + 1] = dexx;
-      dmap[o + 2] = dexy;
-      s_val += S;
-      l1 += fabsf(s_x[(oy + kLR) * kLS + ox + kLR] - s_y[(oy + kLR) * kLS + ox + kLR]);
+      da[p] = 2.f * my * (n2 - n1) * id - 2.f * mx * S * ((d2 - d1) * id);  // 1/d1 - 1/d2
+      db[p] = -S * (d1 * id);
+      dc[p] = 2.f * n1 * id;
+      if (p < m) {
+        s_val += S;
+        l1 += fabsf(x[p] - y[p]);
+      }
     }
+    store_quad(dmap + pix, m, da);
+    store_quad(dmap + map_stride + pix, m, db);
+    store_quad(dmap + 2 * map_stride + pix, m, dc);
   }
-  // fixed-order block sums
+  // fixed-order block sums (their LDS words are the column sums', read by all by now)
   s_val = wave_sum_lane63(s_val);
   l1 = wave_sum_lane63(l1);
+  __syncthreads();
   const int lane = t & (kWave - 1), wave = t / kWave;
   if (lane == kWave - 1) {
-    s_red[0][wave] = s_val;
-    s_red[1][wave] = l1;
+    s_v[wave] = s_val;
+    s_v[4 + wave] = l1;
   }
   __syncthreads();
-  if (t == 0) {
-    bsum[2 * blockIdx.x + 0] = (s_red[0][0] + s_red[0][1]) + (s_red[0][2] + s_red[0][3]);
-    bsum[2 * blockIdx.x + 1] = (s_red[1][0] + s_red[1][1]) + (s_red[1][2] + s_red[1][3]);
-  }
+  if (t < 2) bsum[2 * b + t] = (s_v[4 * t] + s_v[4 * t + 1]) + (s_v[4 * t + 2] + s_v[4 * t + 3]);
 }
 
 __global__ __launch_bounds__(256) void ssim_bwd_kernel(const float* __restrict__ image,
                                                        const float* __restrict__ target, LossViews lv,
-                                                       const float* __restrict__ dmap, float lambda,
-                                                       float* __restrict__ dL) {
-  __shared__ float s_d[3][kLS * kLS];
-  __shared__ float s_h[3][kLS * kLT];
-  const LossTile tl = loss_tile(lv, blockIdx.x);
+                                                       const float* __restrict__ dmap, int64_t map_stride,
+                                                       float lambda, float* __restrict__ dL) {
+  __shared__ float4 s_v4[3 * kLH * kCols / 4];
+  float* s_v = (float*)s_v4;
+  const LossTile tl = loss_tile(lv, xcd_run(blockIdx.x, lv.total_blocks));
   const LossView& q = lv.v[tl.view];
   const int W = q.W, H = q.H, t = threadIdx.x;
   const int64_t plane_px = (int64_t)W * H;
   const int64_t poff = 3 * q.pix_off + tl.plane * plane_px;
-  const int x0 = tl.tx * kLT, y0 = tl.ty * kLT;
-  for (int i = t; i < kLS * kLS; i += 256) {
-    const int r = i / kLS, c = i - r * kLS;
-    const int x = x0 - kLR + c, y = y0 - kLR + r;
-    float a = 0.f, b = 0.f, d = 0.f;
-    if (x >= 0 && x < W && y >= 0 && y < H) {
-      const int64_t o = 3 * (poff + (int64_t)y * W + x);
-      a = dmap[o + 0];
-      b = dmap[o + 1];
-      d = dmap[o + 2];
-    }
-    s_d[0][i] = a;
-    s_d[1][i] = b;
-    s_d[2][i] = d;
-  }
-  __syncthreads();
-  for (int i = t; i < kLS * kLT; i += 256) {
-    const int r = i / kLT, c = i - r * kLT;
-    float a0 = 0.f, a1 = 0.f, a2 = 0.f;
+  const int x0 = tl.tx * kLW, y0 = tl.ty * kLH;
+  {
+    const Column c = column_of(t, x0, y0, W);
+    float d[3][kRows + 2 * kLR];
 #pragma unroll
-    for (int k = 0; k < 11; ++k) {
-      const float g = lv.g[k];
-      a0 += g * s_d[0][r * kLS + c + k];
-      a1 += g * s_d[1][r * kLS + c + k];
-      a2 += g * s_d[2][r * kLS + c + k];
-    }
-    s_h[0][i] = a0;
-    s_h[1][i] = a1;
-    s_h[2][i] = a2;
+    for (int e = 0; e < 3; ++e) load_column(dmap + e * map_stride + poff, c, W, H, d[e]);
+    const int row0 = (t / kCols) * kRows, col = t & (kCols - 1);
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) {
+        float acc = lv.g[0] * d[e][r];
+#pragma unroll
+        for (int k = 1; k < kTaps; ++k) acc += lv.g[k] * d[e][r + k];
+        s_v[(e * kLH + row0 + r) * kCols + col] = acc;
+      }
   }
   __syncthreads();
-  const int ox = out_col(t);
   const float scale = 1.0f / ((float)lv.nviews * 3.0f * (float)plane_px);
+  const int g = t & 31, px = x0 + kQ * g;
+  const int m = g < kLW / kQ ? W - px : 0;
+#pragma unroll 1
+  for (int oy = t / 32; oy < kLH; oy += 8) {
+    const int py = y0 + oy;
+    if (m <= 0 || py >= H) continue;
+    float f[3][kQ];
 #pragma unroll
-  for (int j = 0; j < kLQ; ++j) {
-    const int oy = out_row(t, j);
-    const int px = x0 + ox, py = y0 + oy;
-    if (px >= W || py >= H) continue;
-    float wa = 0.f, wb = 0.f, wc = 0.f;
+    for (int e = 0; e < 3; ++e) filter_row(s_v + (e * kLH + oy) * kCols, g, lv.g, f[e]);
+    const int64_t pix = poff + (int64_t)py * W + px;
+    const Quad x = load_quad(image + pix, m), y = load_quad(target + pix, m);
+    Quad o;
 #pragma unroll
-    for (int k = 0; k < 11; ++k) {
-      const float g = lv.g[k];
-      const int i = (oy + k) * kLT + ox;
-      wa += g * s_h[0][i];
-      wb += g * s_h[1][i];
-      wc += g * s_h[2][i];
+    for (int p = 0; p < kQ; ++p) {
+      const float dsdx = f[0][p] + 2.f * x[p] * f[1][p] + y[p] * f[2][p];
+      const float sg = x[p] > y[p] ? 1.f : (x[p] < y[p] ? -1.f : 0.f);
+      o[p] = ((1.0f - lambda) * sg - lambda * dsdx) * scale;
     }
-    const int64_t gi = poff + (int64_t)py * W + px;
-    const float x = image[gi], y = target[gi];
-    const float dsdx = wa + 2.f * x * wb + y * wc;
-    const float sg = x > y ? 1.f : (x < y ? -1.f : 0.f);
-    dL[gi] = ((1.0f - lambda) * sg - lambda * dsdx) * scale;
+    store_quad(dL + pix, m, o);
   }
 }
 
@@ -243,8 +297,12 @@ hipError_t launch_loss(const LossViews& lv, const float* image, const float* tar
                        float* dL, float* dmap, float* bsum, double* per_view, hipStream_t s) {
   const int nb = lv.total_blocks;
   if (nb == 0) return hipSuccess;
-  hipLaunchKernelGGL(ssim_fwd_kernel, dim3((unsigned)nb), dim3(256), 0, s, image, target, lv, dmap, bsum);
-  if (dL) hipLaunchKernelGGL(ssim_bwd_kernel, dim3((unsigned)nb), dim3(256), 0, s, image, target, lv, dmap, lambda, dL);
+  const LossView& last = lv.v[lv.nviews - 1];
+  const int64_t map_stride = 3 * (last.pix_off + (int64_t)last.W * last.H);  // floats of a map's plane
+  hipLaunchKernelGGL(ssim_fwd_kernel, dim3((unsigned)nb), dim3(256), 0, s, image, target, lv, dmap,
+                     map_stride, bsum);
+  if (dL) hipLaunchKernelGGL(ssim_bwd_kernel, dim3((unsigned)nb), dim3(256), 0, s, image, target, lv, dmap,
+                               map_stride, lambda, dL);
   if (loss) {
     hipLaunchKernelGGL(loss_reduce_kernel, dim3((unsigned)lv.nviews), dim3(256), 0, s, bsum, lv, lambda, per_view, loss);
     hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(64), 0, s, per_view, lv.nviews, loss);
