@@ -678,9 +678,9 @@ int gs_blur_views(const float* in, float* out, const gs_camera* cams, int32_t V,
                   gs_stream_t stream) {
   BlurArgs b;
   int64_t px = 0;
-  if (!loss_views(cams, V, kBlurTile, kBlurTile, &b.views, &px)) return GS_E_INVALID;
-  if (!in || !out || in == out) return GS_E_INVALID;
   if (ksize < 1 || ksize > 2 * kMaxBlurRadius + 1 || ksize % 2 == 0) return GS_E_INVALID;
+  if (!loss_views(cams, V, blur_tile_w((ksize - 1) / 2), kBlurTileH, &b.views, &px)) return GS_E_INVALID;
+  if (!in || !out || in == out) return GS_E_INVALID;
   if (!std::isfinite(sigma) || !(sigma > 0.0f)) return GS_E_INVALID;
   const int d = device_ok();
   if (d != GS_OK) return d;
@@ -699,7 +699,7 @@ int gs_resize_views(const float* in, const gs_camera* in_cams, float* out, const
   if (!in || !out || !in_cams || !out_cams || V < 1 || V > GS_MAX_VIEWS) return GS_E_INVALID;
   ResizeArgs a;
   std::memset(&a, 0, sizeof(a));
-  int64_t io = 0, oo = 0;
+  int64_t io = 0, oo = 0, items = 0;
   for (int v = 0; v < V; ++v) {
     ResizeView& q = a.v[v];
     q.W = in_cams[v].width, q.H = in_cams[v].height;
@@ -707,12 +707,18 @@ int gs_resize_views(const float* in, const gs_camera* in_cams, float* out, const
     if (q.W <= 0 || q.H <= 0 || q.Wo <= 0 || q.Ho <= 0) return GS_E_INVALID;
     q.in_off = io, q.out_off = oo;
     q.inv_area = (float)(1.0 / ((double)q.W * (double)q.H));
+    // n outputs' boxes span at most n W / W' + 2 input columns; one output per thread
+    const int64_t fit = (int64_t)(kResizeCols - 2) * q.Wo / q.W;
+    q.seg = (int32_t)(fit < 1 ? 1 : fit > 256 ? 256 : fit);
+    q.nseg = (int32_t)(((int64_t)q.Wo + q.seg - 1) / q.seg);
+    q.item_off = items;
+    items += 3ll * q.Ho * q.nseg;
     io += (int64_t)q.W * q.H;
     oo += (int64_t)q.Wo * q.Ho;
     if (3 * io >= (1ll << 40) || 3 * oo >= (1ll << 40)) return GS_E_INVALID;
   }
   a.nviews = V;
-  a.total_out = 3 * oo;
+  a.items = items;
   // the buffers must not overlap: every output value reads other input values
   const char *i0 = (const char*)in, *i1 = i0 + 12 * io, *o0 = (const char*)out, *o1 = o0 + 12 * oo;
   if (i0 < o1 && o0 < i1) return GS_E_INVALID;

@@ -103,11 +103,12 @@ struct ProjectBwdArgs {
   int32_t assign;                  // 1: write the parameter gradients (zeros where none), 0: add them
 };
 
-// Views of an image call (loss: 116 x 16 tiles; target blur: 16 x 16): per
+// Views of an image call (loss: 116 x 16 tiles; target blur: blur_tile_w(r) x 16): per
 // view its size, tile grid, pixel offset (views concatenated, each [3][H][W])
 // and first workgroup; the loss window's taps.
 constexpr int kLossTileW = 116, kLossTileH = 16;
-constexpr int kBlurTile = 16;
+constexpr int kBlurTileH = 16;
+__host__ __device__ constexpr int blur_tile_w(int r) { return 128 - (2 * r + 3) / 4 * 4; }
 struct LossView {
   int32_t W, H, TX, TY;
   int64_t pix_off;
@@ -140,7 +141,7 @@ __device__ __forceinline__ LossTile loss_tile(const LossViews& lv, int b) {
   return t;
 }
 
-// Target blur: the views' 16 x 16 tiles, radius r = (k - 1) / 2 and the k taps.
+// Target blur: the views' tiles, radius r = (k - 1) / 2 and the k taps.
 constexpr int kMaxBlurRadius = 15;
 struct BlurArgs {
   LossViews views;
@@ -167,16 +168,22 @@ hipError_t launch_render_fused(const RenderArgs& a, const ViewTable& vt, float* 
                                int32_t* last_contrib, const float* target, const float* scale, float* dL_out,
                                float* grad_pair, uint32_t* sync, hipStream_t s);
 
-// Target resize: per view the input and output sizes and pixel offsets.
+// Target resize: per view the input and output sizes and pixel offsets, the
+// output values of a row that a workgroup takes (their boxes fit kResizeCols
+// input columns where one does), the stretches of a row and the first of the
+// view's 3 H' nseg stretches.
+constexpr int kResizeCols = 1024;
 struct ResizeView {
   int32_t W, H, Wo, Ho;
   int64_t in_off, out_off;
   float inv_area;  // 1 / (W H)
+  int32_t seg, nseg;
+  int64_t item_off;
 };
 struct ResizeArgs {
   ResizeView v[GS_MAX_VIEWS];
   int32_t nviews;
-  int64_t total_out;  // 3 * sum of W' H'
+  int64_t items;
 };
 
 hipError_t launch_blur(const float* in, float* out, const BlurArgs& b, hipStream_t s);
