@@ -33,9 +33,17 @@
 // Forward: lanes whose pixels have terminated drop out of the walk through
 // the exec mask, and a wave leaves once all its pixels are done; the
 // backward's waves vote before each batch and the workgroup leaves once every
-// pixel is done.  The forward evaluates four records' falloff and alpha
-// together (independent of the transmittance) before compositing them in
-// order.  Long lists can be split into forward chunks walked in parallel
+// pixel is done.  At one pixel a thread the forward evaluates four records
+// together and checks once whether a pixel stops among them: its deepest
+// lists are walked by lone waves, bound by the latency of one record's chain
+// (LDS read, exponential, decisions) and of one slice's gather.  With the four
+// records' reads issued together, the transmittance as a plain chain of
+// products and the gathers two slices ahead, the same image took 0.421 ->
+// 0.385 ms for eight views of 1M Gaussians, 0.207 -> 0.175 for lists of 6000
+// entries among 30K, 0.064 -> 0.058 at 200K, 0.021 -> 0.018 at 2K, and the
+// hit counts of the eight views 0.428 -> 0.364.  (Eight records together, or
+// slices further ahead, gain nothing: the registers cost a wave per SIMD.)
+// Long lists can be split into forward chunks walked in parallel
 // (a product pass gives each chunk its starting transmittance; see
 // render_fwd_kernel), which shortens the critical path of the deepest tiles.
 //
@@ -49,6 +57,8 @@
 // pair's emission position: no atomics, so the result is bitwise reproducible.
 #include "gs_common.h"
 #include "kernels.h"
+
+#include <type_traits>
 
 namespace gs {
 
@@ -318,10 +328,9 @@ __device__ __forceinline__ float reduce_scatter9(const float (&x)[GS_GRAD_FLOATS
 //           forward chunking is off): the image, or the chunk's results.
 //   kCount: the same walk, counting instead of blending: per Gaussian, the
 //           number of pixels where it is composited (the ray hits of Eq. 4),
-//           added to a.hits; no image, no chunk states.  Per record and batch,
-//           the waves add their ballot counts into an LDS counter (in place
-//           of the staged colours), flushed to the Gaussian's global counter
-//           once the batch is walked.
+//           added to a.hits; no image, no chunk states.  Lane l keeps the count
+//           of its wave's entry l and adds it to the Gaussian's global counter
+//           once the slice is walked.
 //   kTPass: the product of (1 - alpha) over the chunk's splats that pass the
 //           skip and square tests, ignoring the stop rule (stopped once under
 //           1e-4, where its value no longer matters).
@@ -337,8 +346,26 @@ __device__ __forceinline__ float reduce_scatter9(const float (&x)[GS_GRAD_FLOATS
 // Each chunk of a long list stores its colour, final T and last index;
 // fwd_combine_kernel adds them up.  The critical path of a deep tile becomes
 // about three chunks instead of its whole list.
+typedef float Vec4 __attribute__((ext_vector_type(4)));
+typedef float Vec3 __attribute__((ext_vector_type(3)));
+// A prefetched record's words as a value of their own.  The compiler would
+// otherwise split them into loop-carried scalars, whose register copies wait
+// for the loads that have just been issued.
+template <typename V>
+__device__ __forceinline__ V held(V v) {
+  asm("" : "+v"(v));
+  return v;
+}
+__device__ __forceinline__ Vec3 load3(const float4* p) {
+  const float* f = (const float*)p;
+  return Vec3{f[0], f[1], f[2]};
+}
+
 enum : int { kFull = 0, kCount = 1, kTPass = 2 };
-constexpr int kHalves = 2;  // entries a lane stages per forward group
+// Slices of 64 entries whose records a forward walk has in flight (three while
+// the counting walk, without colours, has the registers).
+template <int MODE>
+constexpr int fwd_ring() { return MODE == kCount ? 3 : 2; }
 // Pixel abscissa of a pixel that has stopped, or lies outside the image: NaN,
 // which no record's square holds (an infinite radius included), so the walk
 // needs no flag per pixel.
@@ -376,15 +403,15 @@ __device__ __forceinline__ float4 get4(const float4* p) {
   return make_float4(get<COH>(f + 0), get<COH>(f + 1), get<COH>(f + 2), get<COH>(f + 3));
 }
 
-// One work item of a forward walk.  s_rec / s_cnt: per wave, the staged group
-// of records (a, b, c) and (COUNT) its hit counts.  Items [0, nfslots) are
+// One work item of a forward walk.  s_rec: per wave, the staged slice
+// of records (a, b, c).  Items [0, nfslots) are
 // the forward chunks that start at a forward boundary (slot order); the rest
 // are each tile's first chunk, in the tile schedule.  Counting walks have no
 // chunk items.  Returns the largest last_contrib this thread stored (0 if none).
 template <int PPT, bool CULL, int MODE, bool COH = false>
 __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt, float* __restrict__ image,
                                          float* __restrict__ T_final, int32_t* __restrict__ last_out, int64_t item,
-                                         float4 (*s_rec)[3][kHalves * kWave], uint32_t (*s_cnt)[kHalves * kWave]) {
+                                         float4 (*s_rec)[3][kWave]) {
   constexpr bool COUNT = MODE == kCount, TPASS = MODE == kTPass;
   const int lf = COUNT ? 31 : a.log2_fchunk;
   const int64_t nfs = COUNT ? 0 : a.nfslots;
@@ -415,11 +442,6 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
   float4* s_a = s_rec[wave][0];
   float4* s_b = s_rec[wave][1];
   float4* s_c = s_rec[wave][2];
-  uint32_t* s_hits = s_cnt[wave];  // COUNT only
-  if (COUNT) {
-#pragma unroll
-    for (int h = 0; h < kHalves; ++h) s_hits[h * kWave + lane] = 0u;
-  }
 
   // C: colour composited so far (the image, summed in list order whatever
   // the tiling); S: colour composited since the last chunk boundary (kept
@@ -474,61 +496,66 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
   uint64_t b0 = (uint64_t)tc.start + ((((uint64_t)cs - tc.start) + ((1ull << lc) - 1)) >> lc << lc);
   if (b0 == (uint64_t)tc.start) b0 += 1ull << lc;
   // Each wave walks its own sub-tile independently (no workgroup barrier), in
-  // groups of up to kHalves x 64 entries (batch_depth if smaller) that never
-  // straddle a chunk boundary: lane l stages entries l and 64 + l of the group
-  // into the wave's LDS, with their culling bits for the wave's live box.  The
-  // records of group g + 1 are loaded into the registers group g was just
-  // staged from, while group g is walked, and the ids of group g + 2 with them.
-  // Late in a deep list most records are culled and a group's walk is much
-  // shorter than a gather's latency, so a walk that lone waves take (the
-  // deepest lists) is bound by one latency per group: two entries a lane halve
-  // the groups.  (Deeper prefetching across groups is undone by the waits the
-  // compiler puts in front of loop-carried loads.)
-  constexpr uint32_t GH = kWave;                         // entries per half group
-  const uint32_t G = (uint32_t)min(kHalves * kWave, a.batch);
-  auto group_end = [&](uint32_t b) -> uint32_t {
-    const uint64_t rel = b - tc.start;
-    const uint64_t next = (uint64_t)tc.start + (((rel >> lc) + 1) << lc);
-    return (uint32_t)min(min((uint64_t)ce, (uint64_t)b + G), next);
-  };
-  uint32_t gs = cs;                                // group g: [gs, ge)
-  uint32_t ge = gs < ce ? group_end(gs) : gs;      // g + 1: [ge, ge2)
-  uint32_t ge2 = ge < ce ? group_end(ge) : ge;     // g + 2: [ge2, ge3)
-  const float4 zf4 = make_float4(0.f, 0.f, 0.f, 0.f);
-  float4 ra[kHalves], rb[kHalves], rc[kHalves];  // records of entries l, 64 + l of the group staged next
-  uint32_t rid[kHalves], nid[kHalves];           // their ids; the ids of the group after it
-  // every lane loads: a lane past a group's end takes the list's last entry,
-  // which is never staged (a load under a lane condition leaves a merged value
+  // slices of 64 entries (fewer with a smaller batch_depth or chunk; a power of
+  // two, so that slices never straddle a chunk boundary): lane l stages entry l
+  // into the wave's LDS, with its culling bits for the wave's live box.  The
+  // records of the next R slices are in flight in R register sets, refilled as
+  // soon as they are staged, and their ids one ring further ahead: late in a
+  // deep list most records are culled, and a slice's walk is much shorter than a
+  // gather's latency.
+  constexpr int R = fwd_ring<MODE>();
+  const uint32_t G = 1u << min(min(6, 31 - __clz(a.batch)), min(lc, lf));  // entries of a slice
+  uint32_t gs = cs;                              // the slice: [gs, gs + G)
+  Vec4 qa[R];                  // records of the slices gs + k G (in turn): (u, v, a, b)
+  Vec3 qb[R], qc[R];           // (c, o', radius) and the colour
+  uint32_t rid[R], nid[R];     // their ids; the ids R slices further on
+  // every lane loads: a lane past a slice's or the list's end takes an entry
+  // that is never staged (a load under a lane condition leaves a merged value
   // whose register copy waits for the load)
   const uint32_t elast = tc.end - 1;  // used only when the walk has entries
 #pragma unroll
-  for (int h = 0; h < kHalves; ++h) {
-    ra[h] = rb[h] = rc[h] = zf4;
-    rid[h] = nid[h] = 0;
+  for (int k = 0; k < R; ++k) {
+    qa[k] = Vec4{0.f, 0.f, 0.f, 0.f};
+    qb[k] = qc[k] = Vec3{0.f, 0.f, 0.f};
+    rid[k] = nid[k] = 0;
   }
+  auto fetch = [&](int k) {
+    const float4* rec = a.splats + (size_t)rid[k] * 3;
+    qa[k] = *(const Vec4*)rec;
+    qb[k] = load3(rec + 1);
+    if (!COUNT) qc[k] = load3(rec + 2);
+  };
   if (cs < ce) {
 #pragma unroll
-    for (int h = 0; h < kHalves; ++h) {
-      rid[h] = a.ids[min(gs + h * GH + lane, elast)];
-      nid[h] = a.ids[min(ge + h * GH + lane, elast)];
-    }
+    for (int k = 0; k < R; ++k) rid[k] = a.ids[min(gs + k * G + lane, elast)];
+    // issued in the order of the loop, so that its waits count on it
 #pragma unroll
-    for (int h = 0; h < kHalves; ++h) {
-      ra[h] = a.splats[(size_t)rid[h] * 3 + 0];
-      rb[h] = a.splats[(size_t)rid[h] * 3 + 1];
-      if (!COUNT) rc[h] = a.splats[(size_t)rid[h] * 3 + 2];
+    for (int k = 0; k < R; ++k) {
+      fetch(k);
+      __builtin_amdgcn_sched_barrier(0);
+      nid[k] = a.ids[min(gs + (R + k) * G + lane, elast)];
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
-  while (gs < ce) {
-    uint64_t live[PPT], alive = 0;
+  // one slice from register set k
+  uint32_t left = ce - cs;  // entries from gs on; 0: the walk is done
+  Box box[PPT];
+  auto walk_slice = [&](int k) {
+    if (k == 0) {  // once a ring: what is still live, and where
+      uint64_t alive = 0;
 #pragma unroll
-    for (int p = 0; p < PPT; ++p) {
-      live[p] = __ballot(!stopped(px[p]));
-      alive |= live[p];
+      for (int p = 0; p < PPT; ++p) {
+        const uint64_t live = __ballot(!stopped(px[p]));
+        alive |= live;
+        if (CULL) {
+          const Box b = live_box(live, a.log2_bw, ox[p], oy[p]);
+          box[p] = PPT > 1 ? b : Box{first_lane(b.x0), first_lane(b.x1), first_lane(b.y0), first_lane(b.y1)};
+        }
+      }
+      if (alive == 0) left = 0;  // every pixel of this wave has stopped
     }
-    if (alive == 0) break;  // every pixel of this wave has stopped
     const uint64_t rel = gs - tc.start;
-    if (MODE == kFull && rel != 0 && (rel & ((1ull << lc) - 1)) == 0) {
+    if (MODE == kFull && left != 0 && rel != 0 && (rel & ((1ull << lc) - 1)) == 0) {
       // a chunk boundary of the backward: record each pixel's transmittance
       // here and the colour of the chunk that ends here, then start a new chunk
       const int64_t slot = (int64_t)(gs >> lc);
@@ -541,163 +568,156 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
       if (lane == 0) a.slot_owner[slot] = (uint32_t)gtile;  // every wave that gets here writes the same
       ++nbnd;
     }
-    const int cnt = (int)(ge - gs);
-    Box box[PPT];
-    if (CULL) {
-#pragma unroll
-      for (int p = 0; p < PPT; ++p) box[p] = live_box(live[p], a.log2_bw, ox[p], oy[p]);
-    }
-    uint32_t bits[kHalves];  // the blocks that the entry may reach
-    uint32_t gid[kHalves];
-#pragma unroll
-    for (int h = 0; h < kHalves; ++h) {
-      const int e = h * (int)GH + lane;
-      bits[h] = e < cnt ? (1u << PPT) - 1u : 0u;
-      if (bits[h]) {  // entry e from the registers
-        s_a[e] = staged_a(ra[h]);
-        s_b[e] = staged_b(rb[h]);
-        if (!COUNT) s_c[e] = rc[h];
-        if (CULL) bits[h] = footprint_mask(ra[h], rb[h], PPT, box);
+    const int cnt = (int)min(G, left);
+    uint32_t bits = lane < cnt ? (1u << PPT) - 1u : 0u;  // the blocks that the entry may reach
+    const Vec4 ha = held(qa[k]);
+    const Vec3 hb = held(qb[k]);
+    const float4 ra = make_float4(ha.x, ha.y, ha.z, ha.w), rb = make_float4(hb.x, hb.y, hb.z, 0.0f);
+    if (bits) {
+      s_a[lane] = staged_a(ra);
+      *(Vec3*)(s_b + lane) = Vec3{kQScale * rb.x, rb.y, rb.z};
+      if (!COUNT) {
+        const Vec3 hc = held(qc[k]);
+        *(Vec3*)(s_c + lane) = hc;
       }
-      gid[h] = rid[h];
+      if (CULL) bits = footprint_mask(ra, rb, PPT, box);
     }
-    // group g + 1's record loads into the registers just staged from, and
-    // group g + 2's id loads
-    const uint32_t ge3 = ge2 < ce ? group_end(ge2) : ge2;
-#pragma unroll
-    for (int h = 0; h < kHalves; ++h) {
-      rid[h] = nid[h];
-      ra[h] = a.splats[(size_t)rid[h] * 3 + 0];
-      rb[h] = a.splats[(size_t)rid[h] * 3 + 1];
-      if (!COUNT) rc[h] = a.splats[(size_t)rid[h] * 3 + 2];
-    }
-    if (ge < ce) {  // uniform; elast is an entry of the walk here
-#pragma unroll
-      for (int h = 0; h < kHalves; ++h) nid[h] = a.ids[min(ge2 + h * GH + lane, elast)];
-    }
-    wave_lds_sync();  // the staged group is visible to the whole wave
-#pragma unroll
-    for (int h = 0; h < kHalves; ++h) {
+    const uint32_t gid = rid[k];
+    rid[k] = nid[k];
+    fetch(k);  // the slice R on, into the registers just staged from
+    nid[k] = a.ids[min(gs + 2 * R * G + lane, elast)];
+    wave_lds_sync();  // the staged slice is visible to the whole wave
     uint64_t mp[PPT], m = 0;  // the entries that reach block p, and their union
 #pragma unroll
     for (int p = 0; p < PPT; ++p) {
-      mp[p] = __ballot((bits[h] >> p) & 1u);
+      mp[p] = __ballot((bits >> p) & 1u);
       m |= mp[p];
     }
     if (m != 0) {
-      // composite one evaluated record into this lane's pixel p.  `gone`: the
-      // lanes whose pixel has stopped since its square tests were made.  Returns
-      // the lanes that take the record.  With several blocks a record's lanes
-      // are selected through the exec mask (three vector operations fewer);
-      // with one they are selected by value, without the branch that would
-      // separate the records' independent evaluations.
-      auto composite = [&](int p, int j, const Eval& e, uint64_t inside, uint64_t& gone, const float4& rc) {
-        const int idx = (int)(gs + j - tc.start) + 1;
-        const float Tn = T[p] * (1.0f - e.alpha);
-        const uint64_t use = inside & ~gone & __ballot(!(e.alpha < kAlphaMin)), low = __ballot(Tn < kTMin);
-        gone |= use & low;  // stop before this splat
-        // the product pass multiplies the stopping splat in as well
-        const uint64_t take = TPASS ? use : use & ~low;
-        const bool in = lane_in(take);
-        if (PPT == 1 || in) {
-          const float w = PPT > 1 || in ? e.alpha * T[p] : 0.0f;
-          C0[p] += rc.x * w;
-          C1[p] += rc.y * w;
-          C2[p] += rc.z * w;
-          S0[p] += rc.x * w;
-          S1[p] += rc.y * w;
-          S2[p] += rc.z * w;
-          T[p] = PPT > 1 || in ? Tn : T[p];
-          last[p] = PPT > 1 || in ? idx : last[p];
-        }
-        return take;
-      };
-      auto stop = [&](int p, uint64_t gone) { px[p] = lane_in(gone) ? kStopped : px[p]; };
-      // COUNT: pixels of this wave that composite record j
-      auto count = [&](int j, uint32_t taken) {
-        if (COUNT && lane == 0 && taken != 0) s_hits[j] += taken;
-      };
       const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-      const int hoff = h * (int)GH;  // bit b of m is entry hoff + b
+      const int idx0 = (int)(gs - tc.start) + 1;  // list position of the slice's entry 0, from 1
+      uint32_t hits = 0;                          // COUNT: lane l's, the pixels that composite entry l
       if constexpr (PPT == 1) {
-        // kIlp records at a time (in list order) while that many are left: their
-        // falloff and alpha do not depend on the transmittance, so the
-        // evaluations run as independent chains before the dependent compositing
-        // steps (no record is guarded on its own, which would let the compiler
-        // sink each evaluation next to its compositing step and serialise the
-        // exponentials' latencies); the last ones one at a time.
-        auto eval_one = [&](int j, Eval& e, uint64_t& in, float4& rc) {
-          const float4 ra = s_a[j], rb = s_b[j];
-          rc = COUNT ? zero4 : s_c[j];
-          eval_splat_all(px[0], py[0], ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, &e);
-          in = lanes_inside(e, rb.z);
-        };
-        uint64_t gone = 0;
-        while (m != 0) {
-          if (__popcll(m) >= kIlp) {  // wave-uniform
-            int jq[kIlp];
+        // N records together (in list order).  Their falloff and alpha do not
+        // depend on the transmittance, and neither do the lanes that use them
+        // unless one stops within the group: with alpha 0 in the other lanes
+        // the transmittance is a chain of N products, checked once at its end
+        // (it only falls).  Only a group in which a pixel stops goes through the
+        // records one by one, to find the lanes that take each.
+        auto group = [&](auto size) {
+          constexpr int N = decltype(size)::value;
+          int jq[N];
+          float4 ra[N], rb[N], rc[N];
+          float al[N], Tq[N + 1];
+          uint64_t use[N], any = 0;
 #pragma unroll
-            for (int q = 0; q < kIlp; ++q) {
-              jq[q] = hoff + __builtin_ctzll(m);
-              m &= m - 1;
-            }
-            float4 rcq[kIlp];
-            Eval eq[kIlp];
-            uint64_t iq[kIlp];
-#pragma unroll
-            for (int q = 0; q < kIlp; ++q) eval_one(jq[q], eq[q], iq[q], rcq[q]);
-#pragma unroll
-            for (int q = 0; q < kIlp; ++q) {
-              const uint64_t take = composite(0, jq[q], eq[q], iq[q], gone, rcq[q]);
-              if (COUNT) count(jq[q], (uint32_t)__popcll(take));
-            }
-          } else {
-            const int j = hoff + __builtin_ctzll(m);
+          for (int q = 0; q < N; ++q) {
+            jq[q] = __builtin_ctzll(m);
             m &= m - 1;
-            float4 rc;
-            Eval e;
-            uint64_t in;
-            eval_one(j, e, in, rc);
-            const uint64_t take = composite(0, j, e, in, gone, rc);
-            if (COUNT) count(j, (uint32_t)__popcll(take));
           }
-        }
-        stop(0, gone);
+#pragma unroll
+          for (int q = 0; q < N; ++q) {
+            ra[q] = s_a[jq[q]];
+            rb[q] = s_b[jq[q]];
+          }
+          // all of the group's reads are in flight before the first is used
+          __builtin_amdgcn_sched_barrier(0);
+          Eval e[N];
+#pragma unroll
+          for (int q = 0; q < N; ++q)
+            eval_splat_all(px[0], py[0], ra[q].x, ra[q].y, ra[q].z, ra[q].w, rb[q].x, rb[q].y, &e[q]);
+#pragma unroll
+          for (int q = 0; q < N; ++q) rc[q] = COUNT || TPASS ? zero4 : s_c[jq[q]];
+#pragma unroll
+          for (int q = 0; q < N; ++q) {
+            al[q] = e[q].alpha;
+            use[q] = lanes_inside(e[q], rb[q].z) & __ballot(!(al[q] < kAlphaMin));
+            any |= use[q];
+          }
+          float am[N];  // alpha of the lanes that take the record, else 0
+          Tq[0] = T[0];
+#pragma unroll
+          for (int q = 0; q < N; ++q) {
+            am[q] = lane_in(use[q]) ? al[q] : 0.0f;
+            Tq[q + 1] = Tq[q] * (1.0f - am[q]);
+          }
+          if ((any & __ballot(Tq[N] < kTMin)) != 0) {  // wave-uniform: some pixel stops here
+            uint64_t gone = 0;
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+              use[q] &= ~gone;
+              const uint64_t low = use[q] & __ballot(Tq[q] * (1.0f - al[q]) < kTMin);
+              gone |= low;                 // stop before this splat
+              if (!TPASS) use[q] &= ~low;  // the product pass multiplies the stopping splat in as well
+              am[q] = lane_in(use[q]) ? al[q] : 0.0f;
+              Tq[q + 1] = Tq[q] * (1.0f - am[q]);
+            }
+            px[0] = lane_in(gone) ? kStopped : px[0];
+          }
+#pragma unroll
+          for (int q = 0; q < N; ++q) {
+            const float w = am[q] * Tq[q];
+            C0[0] += rc[q].x * w;
+            C1[0] += rc[q].y * w;
+            C2[0] += rc[q].z * w;
+            S0[0] += rc[q].x * w;
+            S1[0] += rc[q].y * w;
+            S2[0] += rc[q].z * w;
+            last[0] = lane_in(use[q]) ? idx0 + jq[q] : last[0];
+            if (COUNT) hits = lane_in(1ull << jq[q]) ? (uint32_t)__popcll(use[q]) : hits;
+          }
+          T[0] = Tq[N];
+        };
+        for (int n = __popcll(m); n >= kIlp; n -= kIlp) group(std::integral_constant<int, kIlp>());
+        if (__popcll(m) >= 2) group(std::integral_constant<int, 2>());
+        if (m != 0) group(std::integral_constant<int, 1>());
       } else {
         // one record at a time, over the blocks that it reaches (wave-uniform
-        // branches)
+        // branches).  A record's lanes are selected through the exec mask (three
+        // vector operations fewer than by value).
         for (; m != 0; m &= m - 1) {
-          const int b = __builtin_ctzll(m), j = hoff + b;
-          const float4 ra = s_a[j], rb = s_b[j], rc = COUNT ? zero4 : s_c[j];
+          const int j = __builtin_ctzll(m);
+          const float4 ra = s_a[j], rb = s_b[j], rc = COUNT || TPASS ? zero4 : s_c[j];
           uint32_t taken = 0;
 #pragma unroll
           for (int p = 0; p < PPT; ++p)
-            if ((mp[p] >> b) & 1ull) {
+            if ((mp[p] >> j) & 1ull) {
               Eval e;
               eval_splat_all(px[p], py[p], ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, &e);
-              uint64_t gone = 0;
-              const uint64_t take = composite(p, j, e, lanes_inside(e, rb.z), gone, rc);
-              stop(p, gone);
+              const float Tn = T[p] * (1.0f - e.alpha);
+              const uint64_t use = lanes_inside(e, rb.z) & __ballot(!(e.alpha < kAlphaMin));
+              const uint64_t low = use & __ballot(Tn < kTMin);
+              // the product pass multiplies the stopping splat in as well
+              const uint64_t take = TPASS ? use : use & ~low;
+              if (lane_in(take)) {
+                const float w = e.alpha * T[p];
+                C0[p] += rc.x * w;
+                C1[p] += rc.y * w;
+                C2[p] += rc.z * w;
+                S0[p] += rc.x * w;
+                S1[p] += rc.y * w;
+                S2[p] += rc.z * w;
+                T[p] = Tn;
+                last[p] = idx0 + j;
+              }
+              px[p] = lane_in(low) ? kStopped : px[p];  // stop before this splat
               if (COUNT) taken += (uint32_t)__popcll(take);
             }
-          if (COUNT) count(j, taken);
+          if (COUNT) hits = lane_in(1ull << j) ? taken : hits;
         }
       }
-      if (COUNT) {
-        // flush the half's counters: lane l adds entry hoff + l's hits to its Gaussian
-        wave_lds_sync();
-        const uint32_t hv = hoff + lane < cnt ? s_hits[hoff + lane] : 0u;
-        if (hv != 0) {
-          atomicAdd(a.hits + ((int64_t)gid[h] - (int64_t)tc.view * a.n), hv);
-          s_hits[hoff + lane] = 0u;
-        }
-      }
+      // the slice's counters: lane l adds entry l's hits to its Gaussian
+      if (COUNT && hits != 0) atomicAdd(a.hits + ((int64_t)gid - (int64_t)tc.view * a.n), hits);
     }
-    }
-    wave_lds_sync();  // every lane has read the group before the next one overwrites it
-    gs = ge;
-    ge = ge2;
-    ge2 = ge3;
+    wave_lds_sync();  // every lane has read the slice before the next one overwrites it
+    gs += G;
+    left = left > G ? left - G : 0;
+  };
+  // (no way out between the steps: paths that skip a step's loads would make
+  // the waits of all others wait for the newest load)
+  while (left != 0) {
+#pragma unroll
+    for (int k = 0; k < R; ++k) walk_slice(k);
   }
 
   if (COUNT) return 0;
@@ -772,19 +792,19 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
 }
 
 // Work items [item_base, item_base + gridDim.x) of a forward walk, one per workgroup.
-// The kernel is held to 80, 96 and 128 registers at 1, 2 and 4 pixels a thread
-// (six, five and four waves per SIMD).
+// The kernel is held to 96, 80 and 128 registers at 1, 2 and 4 pixels a thread
+// (five, six and four waves per SIMD).  At 1 it takes 94: held to 80 it spills 11,
+// whose reloads wait for the gathers in flight (200K Gaussians 0.058 -> 0.062 ms).
 template <int PPT>
-constexpr int fwd_waves() { return PPT == 1 ? 6 : PPT == 2 ? 5 : 4; }
+constexpr int fwd_waves() { return PPT == 1 ? 5 : PPT == 2 ? 6 : 4; }
 template <int PPT, bool CULL, int MODE>
 __global__ __launch_bounds__(256, fwd_waves<PPT>()) void render_fwd_kernel(RenderArgs a, ViewTable vt,
                                                                            float* __restrict__ image,
                                                                            float* __restrict__ T_final,
                                                                            int32_t* __restrict__ last_out,
                                                                            int64_t item_base) {
-  __shared__ float4 s_rec[4][3][kHalves * kWave];
-  __shared__ uint32_t s_cnt[4][kHalves * kWave];
-  fwd_item<PPT, CULL, MODE>(a, vt, image, T_final, last_out, (int64_t)blockIdx.x + item_base, s_rec, s_cnt);
+  __shared__ float4 s_rec[4][3][kWave];
+  fwd_item<PPT, CULL, MODE>(a, vt, image, T_final, last_out, (int64_t)blockIdx.x + item_base, s_rec);
 }
 
 // Forward chunking: the tiles with several chunks.  Per pixel, the chunks'
@@ -1291,8 +1311,7 @@ __global__ __launch_bounds__(256, PPT == 1 ? 6 : 1) void render_fused_kernel(Ren
     // the deepest lists' forward walks are the launch's critical path
     __builtin_amdgcn_s_setprio(3);
     int my_max = fwd_item<PPT, CULL, kFull, true>(
-        a, vt, image, T_final, last, q, (float4(*)[3][kHalves * kWave])smem,
-        (uint32_t(*)[kHalves * kWave])(smem + sizeof(float4) * 4 * 3 * kHalves * kWave));
+        a, vt, image, T_final, last, q, (float4(*)[3][kWave])smem);
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) my_max = max(my_max, __shfl_xor(my_max, o, kWave));
     if ((threadIdx.x & (kWave - 1)) == 0) s_wmax[threadIdx.x / kWave] = my_max;
@@ -1410,7 +1429,7 @@ static void fused_ppt(const RenderArgs& a, const ViewTable& vt, float* image, fl
                       const LossIn& loss, float* grad_pair, uint32_t* sync, hipStream_t s) {
   const int nt = tile_threads(a);
   const size_t bwd_sh = lds_bytes(bwd_batch(a.batch, nt / kWave), nt / kWave, true);
-  const size_t fwd_sh = (sizeof(float4) * 4 * 3 + sizeof(uint32_t) * 4) * kHalves * kWave;
+  const size_t fwd_sh = sizeof(float4) * 4 * 3 * kWave;
   const size_t sh = bwd_sh > fwd_sh ? bwd_sh : fwd_sh;
   // forward items, then at most one backward item per tile and one per boundary slot
   const dim3 grid((unsigned)(2 * vt.total_tiles + a.nslots)), block((unsigned)nt);
