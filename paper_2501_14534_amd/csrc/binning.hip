@@ -42,6 +42,11 @@ constexpr int kSortThreads = 512;
 constexpr int kSortItems = 8;
 constexpr int kSortTile = kSortThreads * kSortItems;  // keys per sort block
 constexpr int kRadix = 256;
+// Sort blocks up to which a scatter sums the histogram's rows itself instead of
+// after a launch of their scan: 256 rows of at most 256 bytes a block.  A call on
+// 21 thousand records (six blocks a depth pass, 43 a tile pass): 137 -> 112 us; 49
+// and 407 blocks: four scans of 4 us less, each scatter 1.5 us more.
+constexpr int64_t kScanBlocks = 64;
 
 __device__ __forceinline__ uint32_t effective_count(const uint32_t* count, const int32_t* status) {
   return *status != 0 ? 0u : *count;
@@ -625,11 +630,27 @@ __global__ __launch_bounds__(kSortThreads, 4) void radix_scatter(const uint32_t*
         run += c;
       }
     }
+    // digit t: its elements in earlier blocks, and in all
+    uint32_t before = 0, total = 0;
+    if (t < kRadix) {
+      const uint32_t* row = hist + (int64_t)t * nblk;
+      if (digit_total) {  // uniform: rows scanned
+        before = row[blk];
+        total = digit_total[t];
+      } else {
+  #pragma unroll 8
+        for (int b = 0; b < (int)nact; ++b) {
+          const uint32_t c = row[b];
+          before += b < (int)blk ? c : 0u;
+          total += c;
+        }
+      }
+    }
     const uint32_t lb = exclusive_scan_first_256(run, s_wave);
-    const uint32_t dbase = exclusive_scan_first_256(t < kRadix ? digit_total[t] : 0u, s_wave);
+    const uint32_t dbase = exclusive_scan_first_256(total, s_wave);
     if (t < kRadix) {
       s_lbase[t] = lb;
-      s_gbase[t] = dbase + hist[(int64_t)t * nblk + blk] - lb;
+      s_gbase[t] = dbase + before - lb;
     }
   }
   __syncthreads();
@@ -743,15 +764,231 @@ __global__ __launch_bounds__(256) void tile_order_scatter(const uint32_t* __rest
   if (t < tiles) order[base[g] + rank] = (uint32_t)t;
 }
 
-__global__ void fill_u32(uint32_t* p, int64_t count, uint32_t value) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) p[i] = value;
+// Four words a thread, one store where the address allows it.
+__global__ __launch_bounds__(256) void fill_u32(uint32_t* p, int64_t count, uint32_t value) {
+  const int64_t i = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+  if (((uintptr_t)p & 15) == 0 && i + 4 <= count) {
+    *(uint4*)(p + i) = make_uint4(value, value, value, value);
+  } else {
+    for (int64_t k = i; k < min(i + 4, count); ++k) p[k] = value;
+  }
 }
 
 hipError_t launch_fill_u32(uint32_t* p, int64_t count, uint32_t value, hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(fill_u32, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, p, count, value);
+  hipLaunchKernelGGL(fill_u32, dim3((unsigned)((count + 1023) / 1024)), dim3(256), 0, s, p, count, value);
   return hipGetLastError();
+}
+
+// The lists' ranges and the tile schedule's counters, both zero.
+__global__ __launch_bounds__(256) void clear_ranges(uint32_t* __restrict__ ranges, int64_t words,
+                                                    uint32_t* __restrict__ tile_hist) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < words) ranges[i] = 0u;
+  if (i < 128) tile_hist[i] = 0u;
+}
+
+// Everything up to the emission for at most 1024 ITEMS records, in one
+// workgroup: pair count and capacity status, canonical offsets, the visible
+// records' depth order (stable passes of 8 bits like the general path's, over
+// keys that stay in LDS), their descriptors in that order with the
+// output positions, and each emission chunk's first record: the same words as
+// count_reduce, scan_top, compact_visible, four passes of the radix sort,
+// gather_reduce, scan_top and emit_prefix leave, whose 15 launches of 2 to 8 us
+// are most of a small scene's lists.  The whole call on 2000 records took 134 us
+// with them and takes 52; on 8192, 152 and 72 (112 by the general path); on
+// 12000, 152 and 89 (110).  At 12 records a thread its one workgroup is a match
+// for the general path at some 15 thousand; at 20 it spills and loses.
+constexpr int kSmallThreads = 1024;
+constexpr int64_t small_records(int items) { return (int64_t)kSmallThreads * items; }
+
+template <int ITEMS>
+__global__ __launch_bounds__(kSmallThreads) void small_lists(const float4* __restrict__ splats,
+                                                             const uint32_t* __restrict__ tt, int nrec, int64_t n,
+                                                             ViewTable vt, float inv_tw, float inv_th,
+                                                             uint64_t capacity, uint32_t* __restrict__ count,
+                                                             uint32_t* __restrict__ nvis,
+                                                             int32_t* __restrict__ status,
+                                                             uint32_t* __restrict__ offsets, uint4* desc,
+                                                             uint4* __restrict__ sdesc, uint32_t* __restrict__ epref,
+                                                             uint32_t* __restrict__ chunk_first,
+                                                             uint32_t* __restrict__ drec) {
+  constexpr int kWaves = kSmallThreads / kWave;
+  __shared__ uint32_t s_key[kSmallThreads * ITEMS];
+  __shared__ uint16_t s_idx[kSmallThreads * ITEMS];
+  __shared__ uint16_t s_cnt[kWaves][kRadix];
+  __shared__ uint32_t s_base[kRadix];
+  __shared__ uint32_t s_wave[kWaves];
+  __shared__ uint2 s_part[ITEMS * kWaves];  // per slice and wave: pairs, visible records; then their scans
+  __shared__ unsigned long long s_pairs[kWaves];
+  __shared__ uint32_t s_diff;
+  const int t = threadIdx.x, lane = t & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t / kWave);
+  const uint64_t lt_mask = (1ull << lane) - 1ull;
+  // slices of 1024 consecutive records
+  uint32_t c[ITEMS], ex[ITEMS], vx[ITEMS];
+  unsigned long long sum = 0;
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) c[j] = j * kSmallThreads + t < nrec ? tt[j * kSmallThreads + t] : 0u;
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const uint32_t incl = wave_inclusive_sum(c[j]);
+    const uint64_t vis = __ballot(c[j] != 0u);
+    ex[j] = incl - c[j];
+    vx[j] = (uint32_t)__popcll(vis & lt_mask);
+    sum += c[j];
+    if (lane == kWave - 1) s_part[j * kWaves + wave] = make_uint2(incl, (uint32_t)__popcll(vis));
+  }
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) sum += __shfl_xor(sum, o, kWave);
+  if (lane == 0) s_pairs[wave] = sum;
+  if (t == 0) s_diff = 0u;
+  __syncthreads();
+  constexpr int kParts = ITEMS * kWaves / kWave;  // of a lane
+  static_assert(kParts * kWave == ITEMS * kWaves, "whole lanes");
+  if (wave == 0) {
+    uint2 a[kParts];
+    uint32_t x = 0, y = 0;
+#pragma unroll
+    for (int k = 0; k < kParts; ++k) a[k] = s_part[kParts * lane + k], x += a[k].x, y += a[k].y;
+    uint32_t px = wave_inclusive_sum(x) - x, py = wave_inclusive_sum(y) - y;
+#pragma unroll
+    for (int k = 0; k < kParts; ++k) {
+      s_part[kParts * lane + k] = make_uint2(px, py);
+      px += a[k].x;
+      py += a[k].y;
+    }
+    if (lane == kWave - 1) s_base[0] = py;
+  }
+  unsigned long long K = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) K += s_pairs[w];
+  __syncthreads();
+  const int N = (int)s_base[0];
+  if (t == 0) {
+    *count = K > 0xffffffffull ? 0xffffffffu : (uint32_t)K;
+    *nvis = (uint32_t)N;
+    *status = K > (unsigned long long)capacity ? 1 : 0;
+  }
+  if (K > (unsigned long long)capacity) return;  // overflow: no lists this step (uniform)
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const int r = j * kSmallThreads + t;
+    const uint2 part = s_part[j * kWaves + wave];
+    ex[j] += part.x;
+    vx[j] += part.y;
+    if (r < nrec) offsets[r] = ex[j];
+    if (c[j] == 0u) continue;
+    const float2 uv = *(const float2*)(splats + (int64_t)r * 3);            // u, v
+    const float2 rd = *((const float2*)(splats + (int64_t)r * 3 + 1) + 1);  // radius, depth
+    int v = 0;
+    while (v + 1 < vt.nviews && r >= (int64_t)(v + 1) * n) ++v;
+    const ViewArgs& va = vt.v[v];
+    int x0, y0, x1, y1;
+    tile_rect(uv.x, uv.y, rd.x, inv_tw, inv_th, va.TX, va.TY, &x0, &y0, &x1, &y1);
+    const uint32_t dbits = __float_as_uint(rd.y);  // depth > near plane > 0: bits order as values
+    s_key[vx[j]] = dbits;
+    s_idx[vx[j]] = (uint16_t)vx[j];
+    desc[vx[j]] = make_uint4((uint32_t)(va.tile_off + y0 * va.TX + x0),
+                             (uint32_t)(x1 - x0 + 1) | ((uint32_t)va.TX << 16), ex[j], (uint32_t)r);
+    if (drec) drec[r] = dbits;
+  }
+  __syncthreads();
+  if (N == 0) return;  // uniform
+  // Each wave owns the positions [wave R 64, (wave + 1) R 64), R of at most ITEMS rounds.
+  const int R = (N + kSmallThreads - 1) / kSmallThreads;
+  const int p0 = wave * R * kWave + lane;
+  uint32_t key[ITEMS], idx[ITEMS], pos[ITEMS];
+  {  // the bits in which any two keys differ: a pass over equal digits moves nothing
+    uint32_t diff = 0;
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j)
+      if (j < R && p0 + j * kWave < N) diff |= s_key[p0 + j * kWave] ^ s_key[0];
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) diff |= __shfl_xor(diff, o, kWave);
+    if (lane == 0 && diff != 0u) atomicOr(&s_diff, diff);
+  }
+  __syncthreads();
+  const uint32_t diff = s_diff;
+#pragma unroll 1
+  for (int shift = 0; shift < 32; shift += 8) {
+    if (((diff >> shift) & (kRadix - 1)) == 0u) continue;  // uniform
+#pragma unroll
+    for (int q = 0; q < kWaves * kRadix / 2 / kSmallThreads; ++q) ((uint32_t*)s_cnt)[q * kSmallThreads + t] = 0u;
+    uint16_t* cnt = s_cnt[wave];
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+      const bool valid = j < R && p0 + j * kWave < N;
+      key[j] = valid ? s_key[p0 + j * kWave] : 0u;
+      idx[j] = valid ? s_idx[p0 + j * kWave] : 0u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+      if (j >= R) break;  // uniform
+      const bool valid = p0 + j * kWave < N;
+      const uint32_t d = (key[j] >> shift) & (kRadix - 1);
+      const uint64_t peers = match_digit(d, valid, 8);
+      const uint32_t r = (uint32_t)__popcll(peers & lt_mask);
+      const uint32_t k = valid ? cnt[d] : 0u;  // elements of digit d earlier in this wave
+      pos[j] = k + r;
+      if (valid && r == 0) cnt[d] = (uint16_t)(k + (uint32_t)__popcll(peers));
+      __builtin_amdgcn_wave_barrier();  // the wave's LDS updates stay in item order
+    }
+    __syncthreads();
+    uint32_t run = 0;
+    if (t < kRadix) {
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        const uint32_t k = s_cnt[w][t];
+        s_cnt[w][t] = (uint16_t)run;
+        run += k;
+      }
+    }
+    const uint32_t lb = exclusive_scan_first_256(run, s_wave);
+    if (t < kRadix) s_base[t] = lb;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+      if (j >= R || p0 + j * kWave >= N) continue;
+      const uint32_t d = (key[j] >> shift) & (kRadix - 1);
+      const uint32_t to = s_base[d] + cnt[d] + pos[j];
+      s_key[to] = key[j];
+      s_idx[to] = (uint16_t)idx[j];
+    }
+    __syncthreads();
+  }
+  // depth order: descriptors, output positions, the chunks' first records
+  uint4 d[ITEMS];
+  uint32_t run = 0;
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j)
+    d[j] = j < R && p0 + j * kWave < N ? desc[s_idx[p0 + j * kWave]] : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    c[j] = j < R && p0 + j * kWave < N ? tt[d[j].w] : 0u;
+  }
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const uint32_t incl = wave_inclusive_sum(c[j]);
+    ex[j] = run + incl - c[j];
+    run += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+  }
+  if (lane == 0) s_wave[wave] = run;
+  __syncthreads();
+  uint32_t off = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) off += w < wave ? s_wave[w] : 0u;
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const int m = p0 + j * kWave;
+    if (j >= R || m >= N) continue;
+    const uint32_t e = off + ex[j];
+    sdesc[m] = d[j];
+    epref[m] = e;
+    // chunks whose first position lies in [e, e + c)
+    for (uint64_t q = ((uint64_t)e + kEmitChunk - 1) / kEmitChunk; q * kEmitChunk < (uint64_t)e + c[j]; ++q)
+      chunk_first[q] = (uint32_t)m;
+  }
 }
 
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -828,10 +1065,13 @@ static void radix_sort(KT* k0, uint32_t* v0, uint32_t* u0, KT* k1, uint32_t* v1,
     if (shift > 0 || !counted)
       hipLaunchKernelGGL((radix_hist<KT>), dim3((unsigned)nblk), dim3(kSortThreads), 0, s, kb[cur], count, status,
                          shift, nblk, w.hist);
-    hipLaunchKernelGGL(radix_digit_scan, dim3(kRadix), dim3(256), 0, s, w.hist, nblk, count, status, w.digit_total);
+    // up to kScanBlocks blocks, each sums the rows of the histogram itself
+    uint32_t* totals = nblk > kScanBlocks ? w.digit_total : nullptr;
+    if (totals)
+      hipLaunchKernelGGL(radix_digit_scan, dim3(kRadix), dim3(256), 0, s, w.hist, nblk, count, status, totals);
     hipLaunchKernelGGL((radix_scatter<NV>), dim3((unsigned)nblk), dim3(kSortThreads), 0, s, kb[cur], vb[cur],
                        ub[cur], kb[cur ^ 1], vb[cur ^ 1], ub[cur ^ 1], count, status, shift, bits, nblk, w.hist,
-                       w.digit_total);
+                       totals);
     cur ^= 1;
   }
 }
@@ -840,34 +1080,46 @@ hipError_t launch_bin_sort(const SortPlan& plan, const float4* splats, const uin
                            const ViewTable& vt, float inv_tw, float inv_th, const BinOut& out, uint64_t capacity,
                            void* ws, hipStream_t s) {
   const SortWs w = carve(plan, capacity, ws);
-  hipError_t e;
-  if ((e = launch_fill_u32(out.ranges, 2 * (int64_t)vt.total_tiles, 0u, s)) != hipSuccess) return e;
+  const int64_t words = 2 * (int64_t)vt.total_tiles;
+  if (words > 0)
+    hipLaunchKernelGGL(clear_ranges, dim3((unsigned)(((words > 128 ? words : 128) + 255) / 256)), dim3(256), 0, s,
+                       out.ranges, words, w.tile_hist);
   const int64_t nb = plan.scan_blocks;
   uint32_t* count = out.count;
   int32_t* status = out.status;
   const int64_t rb = plan.rec_blocks;
-  if (rb > 0)
+  // one workgroup is faster than the launches it saves up to here (see small_lists)
+  const bool small = nb > 0 && plan.nrec <= small_records(12);
+  if (rb > 0 && !small)
     hipLaunchKernelGGL(count_reduce, dim3((unsigned)rb), dim3(kScanThreads), 0, s, tiles_touched, plan.nrec,
                        w.block_sums);
   // K and the capacity status, and the number of visible records
-  hipLaunchKernelGGL(scan_top, dim3(1), dim3(1024), 0, s, w.block_sums, rb, (const uint32_t*)nullptr,
-                     capacity, count, w.nvis, status);
+  if (!small)
+    hipLaunchKernelGGL(scan_top, dim3(1), dim3(1024), 0, s, w.block_sums, rb, (const uint32_t*)nullptr,
+                       capacity, count, w.nvis, status);
   if (nb > 0) {
-    hipLaunchKernelGGL(compact_visible, dim3((unsigned)rb), dim3(kScanThreads), 0, s, splats, tiles_touched,
-                       plan.nrec, n, vt, inv_tw, inv_th, w.block_sums, status, out.offsets, w.dkey, w.dval, w.desc,
-                       out.keys ? w.drec : (uint32_t*)nullptr);
-    // depth order of the visible records (four passes: the result is back in dkey/dval)
-    radix_sort<uint32_t, 1>(w.dkey, w.dval, nullptr, w.dkey_alt, w.dval_alt, nullptr, 32, w.nvis, status,
-                            plan.rec_sort_blocks, false, w, s);
     // the emission's positions go to dkey_alt, free after the depth sort
     uint32_t* epref = w.dkey_alt;
-    hipLaunchKernelGGL(gather_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, s, w.desc, w.dval, w.nvis, status,
-                       vt, w.sdesc, epref, w.eblock_sums);
-    hipLaunchKernelGGL(scan_top, dim3(1), dim3(1024), 0, s, w.eblock_sums, nb, w.nvis, (uint64_t)0,
-                       w.nvis + 1, (uint32_t*)nullptr, (int32_t*)nullptr);  // total unused (equals K)
+    if (small) {
+      hipLaunchKernelGGL(plan.nrec <= small_records(8) ? small_lists<8> : small_lists<12>, dim3(1), dim3(kSmallThreads),
+                         0, s, splats, tiles_touched, (int)plan.nrec, n, vt, inv_tw, inv_th, capacity, count, w.nvis,
+                         status, out.offsets, w.desc, w.sdesc, epref, w.chunk_first,
+                         out.keys ? w.drec : (uint32_t*)nullptr);
+    } else {
+      hipLaunchKernelGGL(compact_visible, dim3((unsigned)rb), dim3(kScanThreads), 0, s, splats, tiles_touched,
+                         plan.nrec, n, vt, inv_tw, inv_th, w.block_sums, status, out.offsets, w.dkey, w.dval, w.desc,
+                         out.keys ? w.drec : (uint32_t*)nullptr);
+      // depth order of the visible records (four passes: the result is back in dkey/dval)
+      radix_sort<uint32_t, 1>(w.dkey, w.dval, nullptr, w.dkey_alt, w.dval_alt, nullptr, 32, w.nvis, status,
+                              plan.rec_sort_blocks, false, w, s);
+      hipLaunchKernelGGL(gather_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, s, w.desc, w.dval, w.nvis, status,
+                         vt, w.sdesc, epref, w.eblock_sums);
+      hipLaunchKernelGGL(scan_top, dim3(1), dim3(1024), 0, s, w.eblock_sums, nb, w.nvis, (uint64_t)0,
+                         w.nvis + 1, (uint32_t*)nullptr, (int32_t*)nullptr);  // total unused (equals K)
+      hipLaunchKernelGGL(emit_prefix, dim3((unsigned)nb), dim3(kScanThreads), 0, s, w.nvis, count, w.eblock_sums, status,
+                         epref, w.chunk_first);
+    }
     // emit so that the tile sort ends in (tkey, pair_index, ids)
-    hipLaunchKernelGGL(emit_prefix, dim3((unsigned)nb), dim3(kScanThreads), 0, s, w.nvis, count, w.eblock_sums, status,
-                       epref, w.chunk_first);
     const bool even = (plan.tile_bits + 7) / 8 % 2 == 0;
     const int64_t emit_blocks = ((int64_t)capacity + kEmitChunk - 1) / kEmitChunk;
     if (emit_blocks > 0)
@@ -888,7 +1140,6 @@ hipError_t launch_bin_sort(const SortPlan& plan, const float4* splats, const uin
   if (out.order && vt.total_tiles > 0) {
     const int64_t T = vt.total_tiles;
     const unsigned tb = (unsigned)((T + 255) / 256);
-    if ((e = launch_fill_u32(w.tile_hist, 128, 0u, s)) != hipSuccess) return e;
     hipLaunchKernelGGL(tile_order_count, dim3(tb), dim3(256), 0, s, out.ranges, status, T, w.tile_hist);
     hipLaunchKernelGGL(tile_order_scan, dim3(1), dim3(64), 0, s, w.tile_hist);
     hipLaunchKernelGGL(tile_order_scatter, dim3(tb), dim3(256), 0, s, out.ranges, status, T, w.tile_hist, out.order);
