@@ -52,7 +52,7 @@
 // dividing by (1 - alpha) and carries the dL/dC-weighted colour behind it, so
 // no per-pixel list is stored.  Per-pair partials (9 floats) are summed over
 // the lane's pixels, over the wave (a butterfly reduce-scatter over cross-lane
-// swaps: about 30 instructions for all 9 sums), then over the workgroup's
+// swaps: 43 instructions for the 18 sums of two records), then over the workgroup's
 // waves in a fixed order (LDS), and stored once per (tile, splat) at the
 // pair's emission position: no atomics, so the result is bitwise reproducible.
 #include "gs_common.h"
@@ -287,38 +287,40 @@ __device__ __forceinline__ float dpp_f(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
 }
 
-// Sums each of the 9 per-lane values over the 64 lanes of the wave
-// (butterfly reduce-scatter: every step halves the values a lane carries).
-// Element e ends in the four lanes l with (l >> 2) bits giving
-// k2 = 2 b3 + b2 <= 2, k1 = k2 + 3 b4 <= 4, e = k1 + 5 b5 <= 8; the tree is
-// fixed, so the sum is reproducible.  Needs every lane of the wave active.
-__device__ __forceinline__ float reduce_scatter9(const float (&x)[GS_GRAD_FLOATS], bool b2, bool b3) {
-  float y[5];  // lane bit 5: elements 0-4 stay in lanes 0-31, 5-8 go to lanes 32-63
+// Sums each of 9 per-lane values of two records, x and y, over the 64 lanes of
+// the wave (butterfly reduce-scatter: every step halves the values a lane
+// carries).  The first step folds the halves of x into lanes 0-31 and those of y
+// into lanes 32-63.  Element e = k + 5 b4 of the half's record ends in the two
+// lanes of each (b5, b4, b3, b2, b1) with k: 0: (0, 0, 0), 1: (0, 0, 1),
+// 2: (0, 1, 0), 3: (1, 0, 0), 4: (1, 0, 1) by (b3, b2, b1).  The tree is fixed,
+// so the sums are reproducible, and the same whatever shares the reduction.
+// Needs every lane of the wave active.  43 operations for 18 sums; one record
+// alone takes 31 for its 9, one dependent step after the other.
+__device__ __forceinline__ float reduce_scatter9x2(const float (&x)[GS_GRAD_FLOATS], const float (&y)[GS_GRAD_FLOATS],
+                                                   bool b1, bool b2, bool b3) {
+  float h[GS_GRAD_FLOATS];  // lane bit 5
+#pragma unroll
+  for (int k = 0; k < GS_GRAD_FLOATS; ++k) {
+    float lo = x[k], hi = y[k];
+    swap_halves(lo, hi);
+    h[k] = lo + hi;
+  }
+  float z[5];  // lane bit 4: h0-h4 stay in even rows, h5-h8 go to odd rows
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
-    float lo = x[k], hi = k + 5 < GS_GRAD_FLOATS ? x[k + 5] : 0.0f;
-    swap_halves(lo, hi);
-    y[k] = lo + hi;
-  }
-  float z[3];  // lane bit 4: y0-y2 stay in even rows, y3-y4 go to odd rows
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    float lo = y[k], hi = k + 3 < 5 ? y[k + 3] : 0.0f;
+    float lo = h[k], hi = k + 5 < GS_GRAD_FLOATS ? h[k + 5] : 0.0f;
     swap_rows(lo, hi);
     z[k] = lo + hi;
   }
-  // lane bit 3: row_mirror pairs lane i of a row with lane 15 - i
-  const float t0 = z[0] + dpp_f<0x140>(z[0]);
-  const float t1 = z[1] + dpp_f<0x140>(z[1]);
-  const float t2 = z[2] + dpp_f<0x140>(z[2]);
-  const float w0 = b3 ? t2 : t0;
-  const float w1 = b3 ? 0.0f : t1;
-  // lane bit 2: row_half_mirror pairs lane i of an 8-lane half row with lane 7 - i
-  const float u0 = w0 + dpp_f<0x141>(w0);
-  const float u1 = w1 + dpp_f<0x141>(w1);
-  float v = b2 ? u1 : u0;
-  // lane bits 1 and 0: quad permutations [2,3,0,1] and [1,0,3,2]
-  v += dpp_f<0x4E>(v);
+  float t[5];  // lane bit 3
+#pragma unroll
+  for (int k = 0; k < 5; ++k) t[k] = z[k] + dpp_f<0x140>(z[k]);
+  const float w0 = b3 ? t[3] : t[0], w1 = b3 ? t[4] : t[1], w2 = t[2];
+  const float u0 = w0 + dpp_f<0x141>(w0), u1 = w1 + dpp_f<0x141>(w1), u2 = w2 + dpp_f<0x141>(w2);  // lane bit 2
+  float v0 = b2 ? u2 : u0, v1 = u1;
+  v0 += dpp_f<0x4E>(v0);  // lane bit 1
+  v1 += dpp_f<0x4E>(v1);
+  float v = b1 ? v1 : v0;
   v += dpp_f<0xB1>(v);
   return v;
 }
@@ -934,10 +936,10 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
   float* s_part = L.part;  // per-wave partial sums of one batch: [nwaves][batch][9]
   uint16_t* s_mask = L.mask;
 
-  // this lane's element of the reduce-scatter (see reduce_scatter9)
-  const bool b2 = (lane >> 2) & 1, b3 = (lane >> 3) & 1;
-  const int k2 = 2 * (int)b3 + (int)b2, k1 = k2 + 3 * ((lane >> 4) & 1), my_e = k1 + 5 * ((lane >> 5) & 1);
-  const bool writer = (lane & 3) == 0 && k2 <= 2 && k1 <= 4 && my_e < GS_GRAD_FLOATS;
+  // this lane's element of the reduce-scatter (see reduce_scatter9x2)
+  const bool b1 = (lane >> 1) & 1, b2 = (lane >> 2) & 1, b3 = (lane >> 3) & 1;
+  const int my_k = b3 ? (b1 ? 4 : 3) : b1 ? 1 : b2 ? 2 : 0, my_e = my_k + 5 * ((lane >> 4) & 1);
+  const bool writer = (lane & 1) == 0 && !(b2 && (b1 || b3)) && my_e < GS_GRAD_FLOATS;
   // per element, the factor the walk leaves out: with m = -2 dL/dq,
   // dL/d(u, v) = (-2/k) dL/dq (A dx + B dy, B dx + C dy) = -(2 ln 2) m (a dx + b/2 dy, ...),
   // dL/d(A, B, C) = dL/dq (dx^2, 2 dx dy, dy^2) = -m (dx^2 / 2, dx dy, dy^2 / 2)
@@ -1070,10 +1072,12 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
         continue;
       }
       uint64_t hit = 0;
-      // one staged record: per-pixel partials, then the wave's sums into LDS
-      auto grad = [&](int j, const float4& ra, const float4& rb, const float4& rc) {
-        const int jr = (int)(bs - tc.start) + j;                   // index within the tile's list
-        float x[GS_GRAD_FLOATS] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // m dx, m dy, A B C o' r g b
+      // one staged record's per-pixel partials x (m dx, m dy, A B C o' r g b) over
+      // the lane's pixels; returns the lanes that composite it
+      auto partials = [&](int j, const float4& ra, const float4& rb, const float4& rc, float (&x)[GS_GRAD_FLOATS]) {
+        const int jr = (int)(bs - tc.start) + j;  // index within the tile's list
+#pragma unroll
+        for (int k = 0; k < GS_GRAD_FLOATS; ++k) x[k] = 0.0f;
         uint64_t any = 0;
 #pragma unroll
         for (int p = 0; p < PPT; ++p) {
@@ -1109,31 +1113,37 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
             x[4] += mdy * e.dy;
           }
         }
-        if (any != 0) {  // wave-uniform: the whole wave takes part
-          hit |= 1ull << (j - c * kWave);
-          const float v = reduce_scatter9(x, b2, b3);
-          if (writer) s_part[(wave * batch + j) * GS_GRAD_FLOATS + my_e] = v * escale;
-        }
+        return any;
       };
-      // two register sets in turn: the next record loads while this one is reduced
-      int j0 = c * kWave + (63 - __builtin_clzll(m));  // back to front
-      m &= ~(1ull << (j0 - c * kWave));
-      float4 a0 = s_a[j0], b0 = s_b[j0], c0 = s_c[j0];
-      for (;;) {
-        const bool more1 = m != 0;
-        const int j1 = more1 ? c * kWave + (63 - __builtin_clzll(m)) : j0;
-        m &= ~(1ull << (j1 - c * kWave));
-        const float4 a1 = s_a[j1], b1 = s_b[j1], c1 = s_c[j1];
-        __builtin_amdgcn_sched_barrier(0);  // keep those loads ahead of this record's work
-        grad(j0, a0, b0, c0);
-        if (!more1) break;
-        const bool more2 = m != 0;
-        j0 = more2 ? c * kWave + (63 - __builtin_clzll(m)) : j1;
-        m &= ~(1ull << (j0 - c * kWave));
-        a0 = s_a[j0], b0 = s_b[j0], c0 = s_c[j0];
-        __builtin_amdgcn_sched_barrier(0);
-        grad(j1, a1, b1, c1);
-        if (!more2) break;
+      float* my_part = s_part + wave * batch * GS_GRAD_FLOATS + my_e;
+      // two records at a time, back to front: two independent chains up to the
+      // transmittance, and one reduction (one record at a time, the next one's
+      // reads ahead of it, took 43 us where this takes 40 at 2K Gaussians, 138 -> 131 at
+      // 200K, 407 -> 394 for eight views of 1M, 397 -> 387 at two pixels a thread,
+      // 2520 -> 2493 at four for 6M; reading the next two ahead costs as much again
+      // in register copies)
+      while (m != 0) {
+        const int k0 = 63 - __builtin_clzll(m);
+        m &= ~(1ull << k0);
+        const bool two = m != 0;  // else the second set repeats the first and is left out
+        const int k1 = two ? 63 - __builtin_clzll(m) : k0;
+        m &= ~(1ull << k1);
+        const int j0 = c * kWave + k0, j1 = c * kWave + k1;
+        const float4 a0 = s_a[j0], b0 = s_b[j0], c0 = s_c[j0];
+        const float4 a1 = s_a[j1], bb1 = s_b[j1], c1 = s_c[j1];
+        __builtin_amdgcn_sched_barrier(0);  // all in flight together
+        float x[GS_GRAD_FLOATS], y[GS_GRAD_FLOATS];
+        const uint64_t any0 = partials(j0, a0, b0, c0, x);
+        // a repeated record is left out by its distance
+        const uint64_t any1 = partials(j1, two ? a1 : make_float4(__builtin_nanf(""), a1.y, a1.z, a1.w), bb1, c1, y);
+        if ((any0 | any1) != 0) {  // wave-uniform: the whole wave takes part
+          if (any0 != 0) hit |= 1ull << k0;
+          if (any1 != 0) hit |= 1ull << k1;
+          const float v = reduce_scatter9x2(x, y, b1, b2, b3);
+          const int row = lane < kWave / 2 ? j0 * GS_GRAD_FLOATS : j1 * GS_GRAD_FLOATS;
+          const uint64_t rows = (any0 != 0 ? 0xffffffffull : 0ull) | (any1 != 0 ? 0xffffffffull << 32 : 0ull);
+          if (writer && lane_in(rows)) my_part[row] = v * escale;
+        }
       }
       if (lane == 0) s_hit[c][wave] = hit;
     }
@@ -1172,10 +1182,10 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
   }
 }
 
-// Held to 64, 80 and 96 registers at 1, 2 and 4 pixels a thread: 8, 6 and 5
-// waves per SIMD (at 4 it took 103, 4 waves, without).
+// Takes 63 registers at 1 pixel a thread (eight waves per SIMD); held to 80 and
+// 96 at 2 and 4 (six and five; at 4 it takes 103 without, and 2760 us for 2493).
 template <int PPT>
-constexpr int bwd_waves() { return PPT == 1 ? 8 : PPT == 2 ? 6 : 5; }
+constexpr int bwd_waves() { return PPT <= 2 ? 6 : 5; }
 template <int PPT, bool CULL>
 __global__ __launch_bounds__(256, bwd_waves<PPT>()) void render_bwd_kernel(RenderArgs a, ViewTable vt,
                                                          const float* __restrict__ T_final,
