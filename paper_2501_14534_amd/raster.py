@@ -308,8 +308,9 @@ class RasterizeFn(torch.autograd.Function):
                                "so this image's backward state is gone; use one Rasterizer per forward in flight")
         tensors = ctx.saved_tensors
         params = dict(zip(ctx.names, tensors))
-        # every gradient the call computes is written; at SH degree 0 the band masks get none
-        grads = {k: (torch.zeros_like(v) if rast.deg == 0 and k == "sh_mask_logits" else torch.empty_like(v))
+        # every gradient the call computes is written; the bands and band masks above the SH degree get none
+        used = {"sh_rest": 3 * ((rast.deg + 1) ** 2 - 1) * rast.n, "sh_mask_logits": rast.deg * rast.n}
+        grads = {k: (torch.zeros_like(v) if v.numel() > used.get(k, v.numel()) else torch.empty_like(v))
                  for k, v in params.items()}
         rast.render_bwd(params, dL.contiguous(), grads, assign=True)
         return (None, None, *[grads[k] for k in ctx.names])
