@@ -542,17 +542,27 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
   // one slice from register set k
   uint32_t left = ce - cs;  // entries from gs on; 0: the walk is done
   Box box[PPT];
+  uint64_t was_live[PPT];  // the pixels that the boxes hold
+#pragma unroll
+  for (int p = 0; p < PPT; ++p) {
+    was_live[p] = 0;
+    box[p] = live_box(0, 0, 0.f, 0.f);
+  }
   auto walk_slice = [&](int k) {
     if (k == 0) {  // once a ring: what is still live, and where
+      // (a box is made anew only when its pixels have changed: its chain of scalar
+      // operations is a tenth of a deep list's slice, and four boxes of a 6M-Gaussian
+      // step took 1.35 ms for 1.30)
       uint64_t alive = 0;
 #pragma unroll
       for (int p = 0; p < PPT; ++p) {
         const uint64_t live = __ballot(!stopped(px[p]));
         alive |= live;
-        if (CULL) {
+        if (CULL && live != was_live[p]) {  // uniform
           const Box b = live_box(live, a.log2_bw, ox[p], oy[p]);
           box[p] = PPT > 1 ? b : Box{first_lane(b.x0), first_lane(b.x1), first_lane(b.y0), first_lane(b.y1)};
         }
+        was_live[p] = live;
       }
       if (alive == 0) left = 0;  // every pixel of this wave has stopped
     }
