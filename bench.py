@@ -334,7 +334,7 @@ def main():
     significance = dict(count_hits_ms=round(count_ms, 4), score_ms=round(score_ms, 4), hits_per_call=hit_total,
                         roofline=dict(bound="alu", achieved=round(count_tflops, 3), peak=PEAK_FP32_TFLOPS,
                                       unit="TFLOP/s", frac=round(count_tflops / PEAK_FP32_TFLOPS, 5)),
-                        kernels="render_fwd_kernel<COUNT> + select_hist/pick (4 passes) + significance_kernel")
+                        kernels="render_fwd_kernel<COUNT> + select_hist (4 passes) + significance_kernel")
 
     # ---------------- FP64 oracle on the host cores (bounded sample) ----------------
     cpu = None

@@ -197,10 +197,9 @@ hipError_t launch_mask_loss(const float* m, const float* msh, int64_t n, int deg
 
 // Radix-select state of the volume quantile (significance score).
 struct SelectState {
-  uint32_t prefix;  // key bits chosen so far
-  uint32_t rank;    // rank still wanted among the keys matching the prefix
-  uint32_t pad[2];
-  uint32_t hist[256];
+  uint32_t prefix[4];  // before pass p: key bits chosen so far
+  uint32_t rank[4];    // and the rank still wanted among the keys matching them
+  uint32_t hist[4][256];
 };
 
 hipError_t launch_significance(const float* log_scales, const float* opacity_logits, const float* mask_logits,
