@@ -82,8 +82,9 @@ __device__ __forceinline__ float4 staged_b(float4 rb) {  // (c, o', radius, dept
 // alpha = min(0.99, o' G).  Every operation is explicit (fused multiply-adds
 // written out, no other contraction), so both kernels take identical skip/stop
 // decisions.  Computed without branching; the square test is the caller's.
+// The products a dx and c dy go on to the backward's position gradient.
 struct Eval {
-  float dx, dy, G, raw, alpha;
+  float dx, dy, adx, cdy, G, raw, alpha;
 };
 
 __device__ __forceinline__ void eval_splat_all(float px, float py, float u, float v, float a, float b, float c,
@@ -91,12 +92,16 @@ __device__ __forceinline__ void eval_splat_all(float px, float py, float u, floa
 #pragma clang fp contract(off)
   const float dx = px - u;
   const float dy = py - v;
-  const float t = __builtin_fmaf(b, dy, a * dx);
-  const float ex = __builtin_fmaf(dx, t, (c * dy) * dy);
+  const float adx = a * dx;
+  const float cdy = c * dy;
+  const float t = __builtin_fmaf(b, dy, adx);
+  const float ex = __builtin_fmaf(dx, t, cdy * dy);
   const float G = __builtin_amdgcn_exp2f(ex);
   const float raw = o * G;
   e->dx = dx;
   e->dy = dy;
+  e->adx = adx;
+  e->cdy = cdy;
   e->G = G;
   e->raw = raw;
   e->alpha = fminf(kAlphaMax, raw);

@@ -1082,10 +1082,11 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
         continue;
       }
       uint64_t hit = 0;
-      // one staged record's per-pixel partials x (m dx, m dy, A B C o' r g b) over
-      // the lane's pixels; returns the lanes that composite it
+      // one staged record's per-pixel partials x (u v A B C o' r g b) over the
+      // lane's pixels; returns the lanes that composite it
       auto partials = [&](int j, const float4& ra, const float4& rb, const float4& rc, float (&x)[GS_GRAD_FLOATS]) {
         const int jr = (int)(bs - tc.start) + j;  // index within the tile's list
+        const float hb = 0.5f * ra.w;             // staged b / 2
 #pragma unroll
         for (int k = 0; k < GS_GRAD_FLOATS; ++k) x[k] = 0.0f;
         uint64_t any = 0;
@@ -1111,13 +1112,17 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
             const float dLda = (PPT > 1 || in) && !(e.raw > kAlphaMax) ? T[p] * cd - RdL[p] * inv : 0.0f;
             RdL[p] += cd * wgt;
             x[5] += e.G * dLda;
-            // m = alpha dL/dalpha = -2 dL/dq; what does not depend on the pixel (the
-            // conic in the position gradient, the constant factors) is applied
-            // once, to the sums
+            // m = alpha dL/dalpha = -2 dL/dq; the constant factors are applied once,
+            // to the sums.  The conic of the position gradient is not: along a
+            // needle a dx and b/2 dy nearly cancel in every pixel, and sums of m dx
+            // and m dy, rounded before they meet the conic, leave an error of the
+            // sums' size (half of the rows of 0.55 x 10 and 0.55 x 30 pixel needles
+            // off by 1.9 to 3.1 units of 2^-24 of their products, here by 0.3 to
+            // 0.5; no walk is slower for it).  The products are the evaluation's.
             const float m = e.alpha * dLda;
             const float mdx = m * e.dx, mdy = m * e.dy;
-            x[0] += mdx;
-            x[1] += mdy;
+            x[0] += m * __builtin_fmaf(hb, e.dy, e.adx);
+            x[1] += m * __builtin_fmaf(hb, e.dx, e.cdy);
             x[2] += mdx * e.dx;
             x[3] += mdx * e.dy;
             x[4] += mdy * e.dy;
@@ -1174,16 +1179,8 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
     // fixed-order sum over the waves, one store per (pair, attribute)
     for (int i = threadIdx.x; i < rows * GS_GRAD_FLOATS; i += nthreads) {
       const int r = i / GS_GRAD_FLOATS, k = i - r * GS_GRAD_FLOATS, j = L.row[r];
-      auto total = [&](int e) {
-        float t = s_part[j * GS_GRAD_FLOATS + e];
-        for (int w = 1; w < nwaves; ++w) t += s_part[(w * batch + j) * GS_GRAD_FLOATS + e];
-        return t;
-      };
-      float v = total(k);
-      if (k < 2) {  // sums of m dx and m dy -> position gradient: (a, b/2; b/2, c) of the staged conic
-        const float t = total(1 - k), hb = 0.5f * s_a[j].w;
-        v = k == 0 ? s_a[j].z * v + hb * t : hb * t + s_b[j].x * v;
-      }
+      float v = s_part[j * GS_GRAD_FLOATS + k];
+      for (int w = 1; w < nwaves; ++w) v += s_part[(w * batch + j) * GS_GRAD_FLOATS + k];
       grad_pair[(size_t)s_e[j] * GS_GRAD_FLOATS + k] = v;
       if (k == 0) a.pair_live[s_e[j]] = 1;
     }
