@@ -8,6 +8,7 @@
 
 #include "gs_api.h"
 #include "kernels.h"
+#include "subtiles.h"
 
 using namespace gs;
 
@@ -217,33 +218,15 @@ RenderArgs render_args(const gs_projected* p, const gs_binning* b, const gs_opts
   a.status = b->status;
   a.log2_tw = ilog2(o->tile_w);
   a.log2_th = ilog2(o->tile_h);
-  // one sub-tile of 64 * ppt pixels per wave, as square as the tile allows (wider on ties)
-  const int log2_waves = a.log2_tw + a.log2_th - 6 - ilog2(o->pixels_per_thread);
-  int best = -1;
-  for (int sx = 0; sx <= log2_waves; ++sx) {
-    const int sw = a.log2_tw - sx, sh = a.log2_th - (log2_waves - sx);
-    if (sw < 0 || sh < 0) continue;
-    if (best < 0 || std::abs(sw - sh) < std::abs(a.log2_sw - a.log2_sh) ||
-        (std::abs(sw - sh) == std::abs(a.log2_sw - a.log2_sh) && sw > a.log2_sw)) {
-      best = sx;
-      a.log2_sx = sx;
-      a.log2_sw = sw;
-      a.log2_sh = sh;
-    }
-  }
-  // its ppt blocks of 64 pixels, by the same rule
+  // one sub-tile of 64 * ppt pixels per wave, in ppt blocks of 64 pixels
   const int log2_ppt = ilog2(o->pixels_per_thread);
-  best = -1;
-  for (int bx = 0; bx <= log2_ppt; ++bx) {
-    const int bw = a.log2_sw - bx, bh = a.log2_sh - (log2_ppt - bx);
-    if (bw < 0 || bh < 0) continue;
-    const int d = std::abs(bw - bh), dbest = std::abs(2 * a.log2_bw - 6);
-    if (best < 0 || d < dbest || (d == dbest && bw > a.log2_bw)) {
-      best = bx;
-      a.log2_bx = bx;
-      a.log2_bw = bw;
-    }
-  }
+  const Part sub = split(a.log2_tw, a.log2_th, a.log2_tw + a.log2_th - 6 - log2_ppt);
+  const Part block = split(sub.log2_w, sub.log2_h, log2_ppt);
+  a.log2_sw = sub.log2_w;
+  a.log2_sh = sub.log2_h;
+  a.log2_sx = sub.log2_nx;
+  a.log2_bw = block.log2_w;
+  a.log2_bx = block.log2_nx;
   a.batch = o->batch_depth;
   a.ppt = o->pixels_per_thread;
   a.cull = o->subtile_cull;
