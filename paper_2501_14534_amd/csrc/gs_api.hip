@@ -580,7 +580,7 @@ static bool loss_views(const gs_camera* cams, int32_t V, int tile_w, int tile_h,
     if (W <= 0 || H <= 0) return false;
     LossView& q = lv->v[v];
     q.W = W, q.H = H;
-    q.TX = (W + tile_w - 1) / tile_w, q.TY = (H + tile_h - 1) / tile_h;
+    q.TX = (W - 1) / tile_w + 1, q.TY = (H - 1) / tile_h + 1;  // no sum past the largest int
     q.pix_off = po;
     q.block_off = (int32_t)bo;
     po += (int64_t)W * H;
