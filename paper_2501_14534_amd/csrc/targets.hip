@@ -127,15 +127,18 @@ __global__ __launch_bounds__(256) void resize_kernel(const float* __restrict__ i
     const int64_t row = quotient(li, q.nseg);  // of the three planes' output rows
     const int c = row < Ho ? 0 : row < 2 * (int64_t)Ho ? 1 : 2;
     const int yo = (int)(row - c * (int64_t)Ho);
-    const int xo0 = (int)(li - row * q.nseg) * q.seg, xo1 = min(xo0 + q.seg, Wo), xo = xo0 + t;
-    // input rows of output row yo, columns of outputs [xo0, xo1) and of xo
+    // the stretch's first output and their number: t < nout, since xo0 + t and
+    // xo0 + seg may pass the largest int
+    const int xo0 = (int)(li - row * q.nseg) * q.seg, nout = min(q.seg, Wo - xo0);
+    const int64_t xo = (int64_t)xo0 + t;
+    // input rows of output row yo, columns of the stretch's outputs and of xo
     const int ya = (int)quotient((int64_t)yo * H, Ho), yb = (int)quotient((int64_t)(yo + 1) * H + Ho - 1, Ho);
-    const int sa = (int)quotient((int64_t)xo0 * W, Wo), sb = (int)quotient((int64_t)xo1 * W + Wo - 1, Wo);
-    const int xa = (int)quotient((int64_t)xo * W, Wo), xb = (int)quotient((int64_t)(xo + 1) * W + Wo - 1, Wo);
+    const int sa = (int)quotient((int64_t)xo0 * W, Wo), sb = (int)quotient((int64_t)(xo0 + nout) * W + Wo - 1, Wo);
+    const int64_t xa = quotient(xo * W, Wo), xb = quotient((xo + 1) * W + Wo - 1, Wo);
     const float* src = in + 3 * q.in_off + c * (int64_t)W * H;
     float acc = 0.f;
-    for (int x0 = sa; x0 < sb; x0 += kResizeCols) {  // more than once only if W > kResizeCols W'
-      const int n = min(sb - x0, kResizeCols);
+    for (int64_t x0 = sa; x0 < sb; x0 += kResizeCols) {  // more than once only if W > kResizeCols W'
+      const int n = (int)min(sb - x0, (int64_t)kResizeCols);
       __syncthreads();
       for (int x = 4 * t; x < n; x += 4 * 256) {  // four columns a thread
         Quad col = {0.f, 0.f, 0.f, 0.f};
@@ -151,10 +154,10 @@ __global__ __launch_bounds__(256) void resize_kernel(const float* __restrict__ i
         s_col4[x / 4] = make_float4(col.x, col.y, col.z, col.w);
       }
       __syncthreads();
-      if (xo < xo1)
-        for (int x = max(xa, x0); x < min(xb, x0 + n); ++x) acc += overlap(x, W, xo, Wo) * s_col[x - x0];
+      if (t < nout)
+        for (int64_t x = max(xa, x0); x < min(xb, x0 + n); ++x) acc += overlap(x, W, xo, Wo) * s_col[x - x0];
     }
-    if (xo < xo1) out[3 * q.out_off + row * Wo + xo] = acc * q.inv_area;
+    if (t < nout) out[3 * q.out_off + row * Wo + xo] = acc * q.inv_area;
   }
 }
 

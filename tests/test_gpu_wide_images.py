@@ -1,0 +1,42 @@
+"""Target images at the largest widths that a camera can state (GPU only; 26 GB of planes)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2501_14534_amd import gs, scenes
+
+pytestmark = pytest.mark.gpu
+
+INT_MAX = 2 ** 31 - 1
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    if torch.cuda.mem_get_info()[0] < 64 << 30:
+        pytest.skip("needs 64 GB of free device memory")
+    gs.load()
+    yield
+    torch.cuda.empty_cache()
+
+
+def _cams(w):
+    return gs.cameras([scenes.Camera(np.eye(3, dtype=np.float32), np.zeros(3, np.float32), 1.0, 1.0, 0.0, 0.0, w, 1)])
+
+
+@pytest.mark.parametrize("w,wo", [(INT_MAX, 1000003), (INT_MAX - 512, 1000003), (8, INT_MAX)])
+def test_resize_to_and_from_the_widest_rows(w, wo):
+    """Planes of 1, 2 and 3: a box of n equal values is off by at most n roundings."""
+    src = torch.empty(3, w, device="cuda")
+    for c in range(3):
+        src[c] = c + 1
+    out = torch.full((3, wo), -1.0, device="cuda")
+    print(f"[wide] resize {w} -> {wo}", flush=True)
+    gs.check(gs.resize_views(src.data_ptr(), _cams(w), out.data_ptr(), _cams(wo), 1,
+                             torch.cuda.current_stream().cuda_stream), "gs_resize_views")
+    torch.cuda.synchronize()
+    tol = (w // wo + 2) * 2.0 ** -24
+    for c in range(3):
+        lo, hi = float(out[c].min()), float(out[c].max())
+        assert (c + 1) * (1 - tol) <= lo and hi <= (c + 1) * (1 + tol), (c, lo, hi)
