@@ -1,5 +1,6 @@
 // Tile binning and (tile, depth) ordering of projected records, depth first.
 //
+// Up to the emission, on more than 12288 records:
 //   1. count_reduce + scan_top: device-wide exclusive scans of tiles_touched
 //      (the canonical emission offsets, K and the capacity status) and of
 //      the visibility flags (tiles_touched > 0), 4096 records per block.
@@ -10,25 +11,29 @@
 //      8-bit passes; stable, so equal depths keep record order).
 //   4. gather_reduce gathers the descriptors into depth order once (the only
 //      random access of the emission) and sums the pairs per block;
-//      emit_prefix: each depth-sorted record's first output position;
-//      emit_pairs: the records, now in depth order, emit one (tile, canonical
+//      scan_top and emit_prefix: each depth-sorted record's first output position.
+// On fewer, small_lists leaves the same words in one workgroup, its depth sort in
+// LDS: there the launches are most of the time (measured at small_lists).
+// Then, on any number:
+//   5. emit_pairs: the records, now in depth order, emit one (tile, canonical
 //      pair index, record id) per touched tile into a contiguous
 //      depth-ordered range; each workgroup fills a fixed chunk of output
 //      positions slot by slot (the owning records by a running maximum over the
 //      chunk), so writes are coalesced and neither a big Gaussian nor a block
 //      of them serialises the work.
-//   5. LSD radix sort of the pairs by tile id only (ceil(log2 #tiles) bits,
+//   6. LSD radix sort of the pairs by tile id only (ceil(log2 #tiles) bits,
 //      two passes up to 65536 tiles), carrying pair index and record id.
 //      Stability keeps depth order, and record order among equal depths,
 //      inside every tile: the order of a sort by (tile << 32 | depth bits)
 //      then record id.
-//   6. tile_ranges: [start, end) of every tile and, if asked for, the 64-bit keys.
-//   7. tile_order_*: the heaviest-first tile schedule.
-// The sort passes move 8 bytes per element: 4 passes over the visible
-// records plus 2 over the pairs, instead of 6 passes of 12 bytes over the
-// pairs.  Each pass: per-block digit histogram, per-digit scan across blocks,
-// stable scatter ranked with 64-lane ballots.  Every kernel reads its
-// element count from device memory, so nothing waits for the host.
+//   7. tile_ranges: [start, end) of every tile and, if asked for, the 64-bit keys.
+//   8. tile_order_*: the heaviest-first tile schedule.
+// A pass moves 8 bytes per visible record (4 passes) and 12 per pair (2 passes),
+// instead of 6 passes of 16 over the pairs.  Each: per-block digit histogram (the
+// pairs' first is counted by the emission), per-digit scan across blocks (up to
+// kScanBlocks of them summed by the scatter itself), stable scatter ranked with
+// 64-lane ballots.  Every kernel reads its element count from device memory, so
+// nothing waits for the host.
 #include "gs_common.h"
 #include "kernels.h"
 

@@ -807,6 +807,7 @@ __device__ __forceinline__ int fwd_item(const RenderArgs& a, const ViewTable& vt
 // The kernel is held to 96, 80 and 128 registers at 1, 2 and 4 pixels a thread
 // (five, six and four waves per SIMD).  At 1 it takes 94: held to 80 it spills 11,
 // whose reloads wait for the gathers in flight (200K Gaussians 0.058 -> 0.062 ms).
+// At 2 it spills one, outside of the walk's loop.
 template <int PPT>
 constexpr int fwd_waves() { return PPT == 1 ? 5 : PPT == 2 ? 6 : 4; }
 template <int PPT, bool CULL, int MODE>
@@ -1189,8 +1190,9 @@ __device__ __forceinline__ void bwd_item(const RenderArgs& a, const ViewTable& v
   }
 }
 
-// Takes 63 registers at 1 pixel a thread (eight waves per SIMD); held to 80 and
-// 96 at 2 and 4 (six and five; at 4 it takes 103 without, and 2760 us for 2493).
+// Takes 67 registers at 1 pixel a thread (seven waves per SIMD; its LDS allows
+// six); held to 80 and 96 at 2 and 4 (six and five; at 4 it takes more without,
+// and 2760 us for 2493; held, it spills one).
 template <int PPT>
 constexpr int bwd_waves() { return PPT <= 2 ? 6 : 5; }
 template <int PPT, bool CULL>
@@ -1307,7 +1309,11 @@ __device__ __forceinline__ uint32_t wait_flag(const uint32_t* flag) {
 // walks are still going.  sync: [total_tiles] flags, the ticket, all zero at
 // launch, then the list's counts (kListHist words) and the list.
 // At one pixel a thread the kernel is held to 80 registers (six waves per SIMD,
-// as many as the backward's LDS allows).
+// as many as the backward's LDS allows), though its forward then spills 12.  Held
+// to 96 (five waves, none spilled) it is as fast: eight views of 1M Gaussians in
+// 16 x 16 tiles 1.234 ms for 1.230 at 512-entry backward chunks and 1.571 for 1.577
+// at 256, 200K Gaussians 0.289 for 0.292 and 0.280 for 0.273, in 16 x 8 tiles 0.361
+// for 0.372; not held (99) 1.288, 1.597, 0.306 and 0.288.
 template <int PPT, bool CULL>
 __global__ __launch_bounds__(256, PPT == 1 ? 6 : 1) void render_fused_kernel(RenderArgs a, ViewTable vt,
                                                                              float* __restrict__ image,
