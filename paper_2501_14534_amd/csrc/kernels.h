@@ -121,6 +121,15 @@ struct LossViews {
   float g[11];  // normalised Gaussian taps of the 11 x 11 window's 1-D factor
 };
 
+// Workgroups of an image call, 256 threads each.  A launch holds fewer than 2^32
+// threads along x, so past 2^23 workgroups (a 1 x 4.5e7 image's tiles) they lie in rows
+// of that many; the last row's ends past the last tile.
+constexpr int kImageRow = 1 << 23;
+inline dim3 image_grid(int64_t nb) {
+  return dim3((unsigned)(nb < kImageRow ? nb : kImageRow), (unsigned)((nb + kImageRow - 1) / kImageRow));
+}
+__device__ __forceinline__ int64_t image_block() { return (int64_t)blockIdx.y * kImageRow + blockIdx.x; }
+
 // Workgroup b of an image call: its view, colour plane and tile.
 struct LossTile {
   int view, plane, tx, ty;

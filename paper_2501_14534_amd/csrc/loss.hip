@@ -122,7 +122,8 @@ __global__ __launch_bounds__(256, 4) void ssim_fwd_kernel(const float* __restric
                                                           float* __restrict__ bsum) {
   __shared__ float4 s_v4[5 * kLH * kCols / 4];
   float* s_v = (float*)s_v4;
-  const int b = xcd_run(blockIdx.x, lv.total_blocks);
+  if (image_block() >= lv.total_blocks) return;  // uniform
+  const int b = xcd_run((int)image_block(), lv.total_blocks);
   const LossTile tl = loss_tile(lv, b);
   const LossView& q = lv.v[tl.view];
   const int W = q.W, H = q.H, t = threadIdx.x;
@@ -207,7 +208,8 @@ __global__ __launch_bounds__(256) void ssim_bwd_kernel(const float* __restrict__
                                                        float lambda, float* __restrict__ dL) {
   __shared__ float4 s_v4[3 * kLH * kCols / 4];
   float* s_v = (float*)s_v4;
-  const LossTile tl = loss_tile(lv, xcd_run(blockIdx.x, lv.total_blocks));
+  if (image_block() >= lv.total_blocks) return;  // uniform
+  const LossTile tl = loss_tile(lv, xcd_run((int)image_block(), lv.total_blocks));
   const LossView& q = lv.v[tl.view];
   const int W = q.W, H = q.H, t = threadIdx.x;
   const int64_t plane_px = (int64_t)W * H;
@@ -299,9 +301,9 @@ hipError_t launch_loss(const LossViews& lv, const float* image, const float* tar
   if (nb == 0) return hipSuccess;
   const LossView& last = lv.v[lv.nviews - 1];
   const int64_t map_stride = 3 * (last.pix_off + (int64_t)last.W * last.H);  // floats of a map's plane
-  hipLaunchKernelGGL(ssim_fwd_kernel, dim3((unsigned)nb), dim3(256), 0, s, image, target, lv, dmap,
+  hipLaunchKernelGGL(ssim_fwd_kernel, image_grid(nb), dim3(256), 0, s, image, target, lv, dmap,
                      map_stride, bsum);
-  if (dL) hipLaunchKernelGGL(ssim_bwd_kernel, dim3((unsigned)nb), dim3(256), 0, s, image, target, lv, dmap,
+  if (dL) hipLaunchKernelGGL(ssim_bwd_kernel, image_grid(nb), dim3(256), 0, s, image, target, lv, dmap,
                                map_stride, lambda, dL);
   if (loss) {
     hipLaunchKernelGGL(loss_reduce_kernel, dim3((unsigned)lv.nviews), dim3(256), 0, s, bsum, lv, lambda, per_view, loss);

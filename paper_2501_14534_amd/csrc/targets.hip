@@ -45,7 +45,8 @@ __global__ __launch_bounds__(256) void blur_kernel(const float* __restrict__ in,
   static_assert(kTW + kHalo <= kCols && kTW / kQ <= 32, "tile width");
   __shared__ float4 s_v4[kBlurTileH * kCols / 4];
   float* s_v = (float*)s_v4;
-  const LossTile tl = loss_tile(b.views, blockIdx.x);
+  if (image_block() >= b.views.total_blocks) return;  // uniform
+  const LossTile tl = loss_tile(b.views, (int)image_block());
   const LossView& q = b.views.v[tl.view];
   const int W = q.W, H = q.H, t = threadIdx.x;
   const int64_t poff = 3 * q.pix_off + tl.plane * (int64_t)W * H;
@@ -165,7 +166,7 @@ __global__ __launch_bounds__(256) void resize_kernel(const float* __restrict__ i
 template <int R>
 static void blur_radius(const float* in, float* out, const BlurArgs& b, hipStream_t s) {
   if (b.r == R) {
-    hipLaunchKernelGGL(blur_kernel<R>, dim3((unsigned)b.views.total_blocks), dim3(256), 0, s, in, out, b);
+    hipLaunchKernelGGL(blur_kernel<R>, image_grid(b.views.total_blocks), dim3(256), 0, s, in, out, b);
   } else if constexpr (R > 0) {
     blur_radius<R - 1>(in, out, b, s);
   }
