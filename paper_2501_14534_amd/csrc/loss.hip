@@ -63,9 +63,9 @@ struct Column {
 };
 __device__ __forceinline__ Column column_of(int t, int x0, int y0, int W) {
   Column c;
-  c.x = x0 - kLR + (t & (kCols - 1));
+  c.x = (int)((uint32_t)x0 - kLR + (t & (kCols - 1)));  // past the largest int: negative
   c.y = y0 - kLR + __builtin_amdgcn_readfirstlane(t / kCols) * kRows;
-  c.in = c.x >= 0 && c.x < W;
+  c.in = (uint32_t)c.x < (uint32_t)W;
   return c;
 }
 
@@ -74,9 +74,9 @@ __device__ __forceinline__ void load_column(const float* __restrict__ plane, con
                                             float v[kRows + 2 * kLR]) {
 #pragma unroll
   for (int i = 0; i < kRows + 2 * kLR; ++i) {
-    const int y = c.y + i;
+    const uint32_t y = (uint32_t)c.y + (uint32_t)i;  // rows above the image wrap to the end
     v[i] = 0.0f;
-    if (y >= 0 && y < H && c.in) v[i] = (plane + (int64_t)y * W)[c.x];
+    if (y < (uint32_t)H && c.in) v[i] = (plane + (int64_t)y * W)[c.x];
   }
 }
 
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256, 4) void ssim_fwd_kernel(const float* __restric
   __syncthreads();
   // row pass: 8 rows of 32 threads (29 with pixels), twice
   const int g = t & 31, px = x0 + kQ * g;
-  const int m = g < kLW / kQ ? W - px : 0;
+  const int m = g < kLW / kQ ? (W - x0) - kQ * g : 0;  // (x0 + 4 g may pass the largest int: compare from below)
   float s_val = 0.f, l1 = 0.f;
 #pragma unroll 1
   for (int oy = t / 32; oy < kLH; oy += 8) {
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(256) void ssim_bwd_kernel(const float* __restrict__
   __syncthreads();
   const float scale = 1.0f / ((float)lv.nviews * 3.0f * (float)plane_px);
   const int g = t & 31, px = x0 + kQ * g;
-  const int m = g < kLW / kQ ? W - px : 0;
+  const int m = g < kLW / kQ ? (W - x0) - kQ * g : 0;  // (x0 + 4 g may pass the largest int: compare from below)
 #pragma unroll 1
   for (int oy = t / 32; oy < kLH; oy += 8) {
     const int py = y0 + oy;

@@ -74,7 +74,7 @@ __global__ __launch_bounds__(256) void blur_kernel(const float* __restrict__ in,
   __syncthreads();
   // row pass: 8 rows of 32 threads, twice
   const int g = t & 31, px = x0 + kQ * g;
-  const int m = g < kTW / kQ ? W - px : 0;
+  const int m = g < kTW / kQ ? (W - x0) - kQ * g : 0;  // (x0 + 4 g may pass the largest int: compare from below)
   for (int oy = t / 32; oy < kBlurTileH; oy += 8) {
     const int py = y0 + oy;
     if (m <= 0 || py >= H) continue;
