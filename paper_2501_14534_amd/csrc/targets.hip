@@ -28,12 +28,12 @@ namespace gs {
 
 typedef float Quad __attribute__((ext_vector_type(4), aligned(4)));  // four floats at any float's address
 
-__device__ __forceinline__ int mirror_index(int i, int n) {
+// Position i reflected about 0 and n - 1 (unsigned: the period passes the
+// largest int from n = 2^30 + 2 on).
+__device__ __forceinline__ int64_t mirror_index(int64_t i, int n) {
   if (n == 1) return 0;
-  const int p = 2 * (n - 1);
-  i %= p;
-  if (i < 0) i += p;
-  return i < n ? i : p - i;
+  const uint32_t p = 2u * (uint32_t)(n - 1), k = (uint32_t)(i < 0 ? -i : i) % p;  // even about 0
+  return k < (uint32_t)n ? k : p - k;
 }
 
 template <int R>
@@ -53,15 +53,15 @@ __global__ __launch_bounds__(256) void blur_kernel(const float* __restrict__ in,
   const int x0 = tl.tx * kTW, y0 = tl.ty * kBlurTileH;
   {  // column pass: thread t's column of the window, rows (t / 128) * 8 .. + 8
     const int col = t & (kCols - 1), row0 = __builtin_amdgcn_readfirstlane(t / kCols) * kRows;
-    const float* src = in + poff + mirror_index(x0 - R + col, W);
+    const float* src = in + poff + mirror_index((int64_t)x0 - R + col, W);
     float v[kRows + 2 * R];
-    const int ya = y0 + row0 - R;
+    const int64_t ya = (int64_t)y0 + row0 - R;
     if (ya >= 0 && ya + kRows + 2 * R <= H) {  // no row of the wave's is reflected
 #pragma unroll
-      for (int i = 0; i < kRows + 2 * R; ++i) v[i] = src[(int64_t)(ya + i) * W];
+      for (int i = 0; i < kRows + 2 * R; ++i) v[i] = src[(ya + i) * W];
     } else {
 #pragma unroll
-      for (int i = 0; i < kRows + 2 * R; ++i) v[i] = src[(int64_t)mirror_index(ya + i, H) * W];
+      for (int i = 0; i < kRows + 2 * R; ++i) v[i] = src[mirror_index(ya + i, H) * W];
     }
 #pragma unroll
     for (int r = 0; r < kRows; ++r) {

@@ -66,3 +66,27 @@ def test_loss_of_the_longest_images(w, h):
             inner = out[c * n + 16:(c + 1) * n - 16]
             grads += [float(inner.min()) * n, float(inner.max()) * n]
     assert np.abs(np.array(grads) / grads[0] - 1.0).max() <= 2.0 ** -20, grads
+
+
+@pytest.mark.parametrize("w", [2 ** 30 + 1, 2 ** 30 + 2, INT_MAX])
+def test_blur_reflects_at_the_ends_of_the_widest_rows(w):
+    """Zeros but for 1 .. 8 from either end of a row: with 7 taps the 5 values at either end are those of
+    the row's first 16 values alone, and the middle is zero."""
+    r, k, sigma = 3, 7, 1.5
+    src = torch.zeros(3, w, device="cuda")
+    ramp = torch.arange(1, 9, device="cuda", dtype=torch.float32)
+    src[:, :8] = ramp
+    src[:, -8:] = ramp.flip(0)
+    small = torch.zeros(3, 16, device="cuda")
+    small[:, :8] = ramp
+    out, ref = torch.full((3, w), -1.0, device="cuda"), torch.empty(3, 16, device="cuda")
+    print(f"[wide] blur {w}", flush=True)
+    s = torch.cuda.current_stream().cuda_stream
+    gs.check(gs.blur_views(small.data_ptr(), ref.data_ptr(), _cams(16), 1, k, sigma, s), "gs_blur_views")
+    gs.check(gs.blur_views(src.data_ptr(), out.data_ptr(), _cams(w), 1, k, sigma, s), "gs_blur_views")
+    torch.cuda.synchronize()
+    assert torch.equal(out[:, :5], ref[:, :5])
+    assert torch.allclose(out[:, -5:], ref[:, :5].flip(1), rtol=2 * k * 2.0 ** -24, atol=0)
+    for c in range(3):
+        lo, hi = out[c, 8 + r:-8 - r].min(), out[c, 8 + r:-8 - r].max()
+        assert float(lo) == 0.0 and float(hi) == 0.0
