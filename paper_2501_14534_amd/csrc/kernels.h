@@ -192,7 +192,9 @@ struct ResizeView {
 struct ResizeArgs {
   ResizeView v[GS_MAX_VIEWS];
   int32_t nviews;
+  int32_t by_box;     // one thread per output value instead
   int64_t items;
+  int64_t total_out;  // 3 * sum of W' H'
 };
 
 hipError_t launch_blur(const float* in, float* out, const BlurArgs& b, hipStream_t s);

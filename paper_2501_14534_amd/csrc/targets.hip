@@ -15,12 +15,15 @@
 // Resize: every output value averages the input over its box
 // [x' W / W', (x' + 1) W / W') x [y' H / H', (y' + 1) H / H').  Overlaps
 // are integers in units of 1 / W' (1 / H'), so the weights are exact; the sum
-// is divided by W H once.  A workgroup takes a stretch of one output row whose
-// boxes cover about 1000 input columns: its threads sum the box's rows per
-// input column, side by side in memory, into LDS, then each output value adds
-// its columns.  (A thread per output value, walking its box alone, leaves the
-// chip idle when the output is small and reads 4 bytes of every W / W' columns
-// at once: three views of 5.9 M values to an eighth took 18 us, now 11.)
+// is divided by W H once.  Two kernels (the rule and its figures: resize_by_box
+// in gs_api.hip).  Boxes of few pixels, and narrow outputs: a thread per output
+// value walks its box.  Large boxes, where such threads would be few, each with
+// a long chain of loads W / W' columns apart: a workgroup takes a stretch of one
+// output row whose boxes cover about 1000 input columns; its threads sum the
+// box's rows per input column, side by side in memory, into LDS, then each
+// output value adds its columns (three views of 5.9 M values to an eighth 18 ->
+// 11 us; at a half or full size 1.3 to 1.5 times as slow as by box, and 5 to 50
+// times for rows of 64 to 3 pixels).
 #include "gs_common.h"
 #include "kernels.h"
 
@@ -114,6 +117,32 @@ __device__ __forceinline__ float overlap(int64_t i, int64_t n, int64_t o, int64_
   return (float)(min((i + 1) * no, (o + 1) * n) - max(i * no, o * n));
 }
 
+__global__ __launch_bounds__(256) void resize_box_kernel(const float* __restrict__ in, float* __restrict__ out,
+                                                         ResizeArgs a) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= a.total_out) return;
+  int v = 0;
+  while (v + 1 < a.nviews && e >= 3 * a.v[v + 1].out_off) ++v;
+  const ResizeView& q = a.v[v];
+  const int64_t plane_out = (int64_t)q.Wo * q.Ho;
+  const int64_t le = e - 3 * q.out_off;
+  const int c = (int)(le / plane_out);
+  const int64_t p = le - c * plane_out;
+  const int yo = (int)(p / q.Wo), xo = (int)(p - (int64_t)yo * q.Wo);
+  const int W = q.W, H = q.H, Wo = q.Wo, Ho = q.Ho;
+  // input pixels whose box overlaps output pixel (xo, yo)
+  const int xa = (int)(((int64_t)xo * W) / Wo), xb = (int)(((int64_t)(xo + 1) * W + Wo - 1) / Wo);
+  const int ya = (int)(((int64_t)yo * H) / Ho), yb = (int)(((int64_t)(yo + 1) * H + Ho - 1) / Ho);
+  const float* src = in + 3 * q.in_off + c * (int64_t)W * H;
+  float acc = 0.f;
+  for (int y = ya; y < yb; ++y) {
+    float row = 0.f;
+    for (int x = xa; x < xb; ++x) row += overlap(x, W, xo, Wo) * src[(int64_t)y * W + x];
+    acc += overlap(y, H, yo, Ho) * row;
+  }
+  out[e] = acc * q.inv_area;
+}
+
 __global__ __launch_bounds__(256) void resize_kernel(const float* __restrict__ in, float* __restrict__ out,
                                                      ResizeArgs a) {
   __shared__ float4 s_col4[kResizeCols / 4];
@@ -180,6 +209,10 @@ hipError_t launch_blur(const float* in, float* out, const BlurArgs& b, hipStream
 
 hipError_t launch_resize(const float* in, float* out, const ResizeArgs& a, hipStream_t s) {
   if (a.items == 0) return hipSuccess;
+  if (a.by_box) {
+    hipLaunchKernelGGL(resize_box_kernel, dim3((unsigned)((a.total_out + 255) / 256)), dim3(256), 0, s, in, out, a);
+    return hipGetLastError();
+  }
   const int64_t grid = a.items < (1 << 20) ? a.items : (1 << 20);
   hipLaunchKernelGGL(resize_kernel, dim3((unsigned)grid), dim3(256), 0, s, in, out, a);
   return hipGetLastError();
