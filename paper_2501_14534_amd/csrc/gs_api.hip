@@ -582,6 +582,8 @@ static bool loss_views(const gs_camera* cams, int32_t V, int tile_w, int tile_h,
     LossView& q = lv->v[v];
     q.W = W, q.H = H;
     q.TX = (W - 1) / tile_w + 1, q.TY = (H - 1) / tile_h + 1;  // no sum past the largest int
+    const int last = W - (q.TX - 1) * tile_w;
+    q.tw = last > kFewColumns ? tile_w : (W / q.TX + (W % q.TX != 0) + 3) / 4 * 4;  // whole quads, at most tile_w
     q.pix_off = po;
     q.block_off = (int32_t)bo;
     po += (int64_t)W * H;

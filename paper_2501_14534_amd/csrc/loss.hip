@@ -131,7 +131,7 @@ __global__ __launch_bounds__(256, 4) void ssim_fwd_kernel(const float* __restric
   const int64_t poff = 3 * q.pix_off + tl.plane * plane_px;  // this plane in the view-concatenated layout
   const float* xp = image + poff;
   const float* yp = target + poff;
-  const int x0 = tl.tx * kLW, y0 = tl.ty * kLH;
+  const int x0 = tl.tx * q.tw, y0 = tl.ty * kLH;
   {  // column pass
     const Column c = column_of(t, x0, y0, W);
     float x[kRows + 2 * kLR], y[kRows + 2 * kLR];
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256, 4) void ssim_fwd_kernel(const float* __restric
   __syncthreads();
   // row pass: 8 rows of 32 threads (29 with pixels), twice
   const int g = t & 31, px = x0 + kQ * g;
-  const int m = g < kLW / kQ ? (W - x0) - kQ * g : 0;  // (x0 + 4 g may pass the largest int: compare from below)
+  const int m = kQ * g < q.tw ? (W - x0) - kQ * g : 0;  // (x0 + 4 g may pass the largest int: compare from below)
   float s_val = 0.f, l1 = 0.f;
 #pragma unroll 1
   for (int oy = t / 32; oy < kLH; oy += 8) {
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(256) void ssim_bwd_kernel(const float* __restrict__
   const int W = q.W, H = q.H, t = threadIdx.x;
   const int64_t plane_px = (int64_t)W * H;
   const int64_t poff = 3 * q.pix_off + tl.plane * plane_px;
-  const int x0 = tl.tx * kLW, y0 = tl.ty * kLH;
+  const int x0 = tl.tx * q.tw, y0 = tl.ty * kLH;
   {
     const Column c = column_of(t, x0, y0, W);
     float d[3][kRows + 2 * kLR];
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(256) void ssim_bwd_kernel(const float* __restrict__
   __syncthreads();
   const float scale = 1.0f / ((float)lv.nviews * 3.0f * (float)plane_px);
   const int g = t & 31, px = x0 + kQ * g;
-  const int m = g < kLW / kQ ? (W - x0) - kQ * g : 0;  // (x0 + 4 g may pass the largest int: compare from below)
+  const int m = kQ * g < q.tw ? (W - x0) - kQ * g : 0;  // (x0 + 4 g may pass the largest int: compare from below)
 #pragma unroll 1
   for (int oy = t / 32; oy < kLH; oy += 8) {
     const int py = y0 + oy;

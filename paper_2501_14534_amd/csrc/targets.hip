@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void blur_kernel(const float* __restrict__ in,
   const LossView& q = b.views.v[tl.view];
   const int W = q.W, H = q.H, t = threadIdx.x;
   const int64_t poff = 3 * q.pix_off + tl.plane * (int64_t)W * H;
-  const int x0 = tl.tx * kTW, y0 = tl.ty * kBlurTileH;
+  const int x0 = tl.tx * q.tw, y0 = tl.ty * kBlurTileH;
   {  // column pass: thread t's column of the window, rows (t / 128) * 8 .. + 8
     const int col = t & (kCols - 1), row0 = __builtin_amdgcn_readfirstlane(t / kCols) * kRows;
     const float* src = in + poff + mirror_index((int64_t)x0 - R + col, W);
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(256) void blur_kernel(const float* __restrict__ in,
   __syncthreads();
   // row pass: 8 rows of 32 threads, twice
   const int g = t & 31, px = x0 + kQ * g;
-  const int m = g < kTW / kQ ? (W - x0) - kQ * g : 0;  // (x0 + 4 g may pass the largest int: compare from below)
+  const int m = kQ * g < q.tw ? (W - x0) - kQ * g : 0;  // (x0 + 4 g may pass the largest int: compare from below)
   for (int oy = t / 32; oy < kBlurTileH; oy += 8) {
     const int py = y0 + oy;
     if (m <= 0 || py >= H) continue;
