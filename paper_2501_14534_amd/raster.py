@@ -343,7 +343,7 @@ class Step:
     sparse SH update the paper adopts (Sec. 3.2.5); two graphs are captured and
     replayed in turn.  fused (loss "l2" only): the forward walk, the loss
     gradient and the backward walk run as one launch (gs_render_fwd_bwd_l2),
-    with the same results as the three separate calls (1.06 to 1.6 times as
+    with the same results as the three separate calls (1.1 to 1.6 times as
     slow on the five benchmark workloads, so off by default).
 
     The binning capacity is fixed while a graph exists; `run()` reads the
