@@ -119,11 +119,10 @@ __device__ __forceinline__ void store_quad(float* p, int m, Quad q) {
 __global__ __launch_bounds__(256, 4) void ssim_fwd_kernel(const float* __restrict__ image,
                                                           const float* __restrict__ target, LossViews lv,
                                                           float* __restrict__ dmap, int64_t map_stride,
-                                                          float* __restrict__ bsum) {
+                                                          float* __restrict__ bsum, int first) {
   __shared__ float4 s_v4[5 * kLH * kCols / 4];
   float* s_v = (float*)s_v4;
-  if (image_block() >= lv.total_blocks) return;  // uniform
-  const int b = xcd_run((int)image_block(), lv.total_blocks);
+  const int b = xcd_run(first + (int)blockIdx.x, lv.total_blocks);
   const LossTile tl = loss_tile(lv, b);
   const LossView& q = lv.v[tl.view];
   const int W = q.W, H = q.H, t = threadIdx.x;
@@ -205,11 +204,10 @@ __global__ __launch_bounds__(256, 4) void ssim_fwd_kernel(const float* __restric
 __global__ __launch_bounds__(256) void ssim_bwd_kernel(const float* __restrict__ image,
                                                        const float* __restrict__ target, LossViews lv,
                                                        const float* __restrict__ dmap, int64_t map_stride,
-                                                       float lambda, float* __restrict__ dL) {
+                                                       float lambda, float* __restrict__ dL, int first) {
   __shared__ float4 s_v4[3 * kLH * kCols / 4];
   float* s_v = (float*)s_v4;
-  if (image_block() >= lv.total_blocks) return;  // uniform
-  const LossTile tl = loss_tile(lv, xcd_run((int)image_block(), lv.total_blocks));
+  const LossTile tl = loss_tile(lv, xcd_run(first + (int)blockIdx.x, lv.total_blocks));
   const LossView& q = lv.v[tl.view];
   const int W = q.W, H = q.H, t = threadIdx.x;
   const int64_t plane_px = (int64_t)W * H;
@@ -301,10 +299,13 @@ hipError_t launch_loss(const LossViews& lv, const float* image, const float* tar
   if (nb == 0) return hipSuccess;
   const LossView& last = lv.v[lv.nviews - 1];
   const int64_t map_stride = 3 * (last.pix_off + (int64_t)last.W * last.H);  // floats of a map's plane
-  hipLaunchKernelGGL(ssim_fwd_kernel, image_grid(nb), dim3(256), 0, s, image, target, lv, dmap,
-                     map_stride, bsum);
-  if (dL) hipLaunchKernelGGL(ssim_bwd_kernel, image_grid(nb), dim3(256), 0, s, image, target, lv, dmap,
-                               map_stride, lambda, dL);
+  image_launches(nb, [&](int first, dim3 grid) {
+    hipLaunchKernelGGL(ssim_fwd_kernel, grid, dim3(256), 0, s, image, target, lv, dmap, map_stride, bsum, first);
+  });
+  if (dL)
+    image_launches(nb, [&](int first, dim3 grid) {
+      hipLaunchKernelGGL(ssim_bwd_kernel, grid, dim3(256), 0, s, image, target, lv, dmap, map_stride, lambda, dL, first);
+    });
   if (loss) {
     hipLaunchKernelGGL(loss_reduce_kernel, dim3((unsigned)lv.nviews), dim3(256), 0, s, bsum, lv, lambda, per_view, loss);
     hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(64), 0, s, per_view, lv.nviews, loss);

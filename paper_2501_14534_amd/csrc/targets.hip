@@ -41,15 +41,14 @@ __device__ __forceinline__ int64_t mirror_index(int64_t i, int n) {
 
 template <int R>
 __global__ __launch_bounds__(256) void blur_kernel(const float* __restrict__ in, float* __restrict__ out,
-                                                   BlurArgs b) {
+                                                   BlurArgs b, int first) {
   constexpr int kCols = 128, kRows = kBlurTileH / 2, kQ = 4;
   constexpr int kTW = blur_tile_w(R);                     // output columns
   constexpr int kHalo = (2 * R + kQ - 1) / kQ * kQ;       // the row pass reads whole quads
   static_assert(kTW + kHalo <= kCols && kTW / kQ <= 32, "tile width");
   __shared__ float4 s_v4[kBlurTileH * kCols / 4];
   float* s_v = (float*)s_v4;
-  if (image_block() >= b.views.total_blocks) return;  // uniform
-  const LossTile tl = loss_tile(b.views, (int)image_block());
+  const LossTile tl = loss_tile(b.views, first + (int)blockIdx.x);
   const LossView& q = b.views.v[tl.view];
   const int W = q.W, H = q.H, t = threadIdx.x;
   const int64_t poff = 3 * q.pix_off + tl.plane * (int64_t)W * H;
@@ -195,7 +194,9 @@ __global__ __launch_bounds__(256) void resize_kernel(const float* __restrict__ i
 template <int R>
 static void blur_radius(const float* in, float* out, const BlurArgs& b, hipStream_t s) {
   if (b.r == R) {
-    hipLaunchKernelGGL(blur_kernel<R>, image_grid(b.views.total_blocks), dim3(256), 0, s, in, out, b);
+    image_launches(b.views.total_blocks, [&](int first, dim3 grid) {
+      hipLaunchKernelGGL(blur_kernel<R>, grid, dim3(256), 0, s, in, out, b, first);
+    });
   } else if constexpr (R > 0) {
     blur_radius<R - 1>(in, out, b, s);
   }
